@@ -129,8 +129,9 @@ int64_t pact_digest_slots(const pact_shard* s);
 
 /* Bytes of device workspace that lets a call spread its digest partial sums
  * over several memory locations (16 lanes, 256 bytes apart, per digest slot)
- * instead of funnelling one 64-bit atomic per 4096-element tile into a single
- * address, which serializes on large shards.  The caller allocates it (8-byte
+ * instead of funnelling one 64-bit atomic per tile into a single address,
+ * which serializes on large shards, and lets its last tile write each result,
+ * with no launch behind the tiles.  The caller allocates it (8-byte
  * aligned, disjoint from every other buffer) and may reuse it for any later
  * call on the same stream.  Its contents on entry do not matter (the call
  * clears the part it uses first, unless told with PACT_COMMIT_WORKSPACE_CLEAN
@@ -160,8 +161,9 @@ int pact_adamw_commit(const pact_shard* s, uint64_t step, const pact_hyper* hype
  * PACT_COMMIT_WORKSPACE_CLEAN: the caller vouches that the workspace is clear
  * (zero-filled before its first use, and touched since then only by calls on
  * this stream that returned PACT_OK), so the call skips the launch that
- * clears it; a workspace in any other state gives a wrong digest.  Without a
- * workspace the flag has no effect.  Unknown flag bits are PACT_EINVAL. */
+ * clears it; a workspace in any other state gives a wrong digest (or leaves
+ * the digest slots as they were).  Without a workspace the flag has no effect.
+ * Unknown flag bits are PACT_EINVAL. */
 int pact_adamw_commit_ex(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags);
 
 /* For callers that cannot allocate device memory (code under HIP graph
@@ -232,6 +234,33 @@ int pact_adamw_commit_bf16(const pact_shard_bf16* s, uint64_t step, const pact_h
 
 /* Digest of the current BF16 (p, m, v); grad is not read and may be NULL. */
 int pact_shard_digest_bf16(const pact_shard_bf16* s);
+
+/* What a caller knows about one shard's workspace between calls.  All zero
+ * for one of unknown contents; clear = 1 and stream set for one that was
+ * zero-filled on that stream.  The library keeps it up to date; the caller
+ * sets clear = 0 after it has written to the workspace itself. */
+typedef struct pact_workspace_state {
+    void* stream;   /* the stream of the last call                                  */
+    uint32_t clear; /* the workspace is zero once that stream has run its last call */
+    uint32_t odd;   /* which of the workspace's two sets the next call uses         */
+} pact_workspace_state;
+
+/* The calls above, in the state `ws` (NULL: nothing is known, the call is
+ * exactly the one above).  A call clears the workspace first unless the state
+ * says that it is clear and that its last call was on this stream.  The
+ * workspace holds two sets of partial sums: successive calls alternate, and
+ * each also clears the other's set, so a workspace that was written to behind
+ * the state's back costs one wrong result (or one left as it was) and no more.
+ * A state belongs to one workspace and, as the workspace, to one call at a
+ * time.  flags: 0 or PACT_COMMIT_ZERO_GRAD. */
+int pact_adamw_commit_ws(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags,
+                         pact_workspace_state* ws);
+int pact_grad_guard_ws(const pact_shard* s, uint64_t* dev_out, pact_workspace_state* ws);
+int pact_shard_digest_ws(const pact_shard* s, pact_workspace_state* ws);
+int pact_bf16_digest_ws(const pact_shard* s, uint64_t* dev_out, pact_workspace_state* ws);
+int pact_adamw_commit_bf16_ws(const pact_shard_bf16* s, uint64_t step, const pact_hyper* hyper,
+                              pact_workspace_state* ws);
+int pact_shard_digest_bf16_ws(const pact_shard_bf16* s, pact_workspace_state* ws);
 
 /* Slot count and workspace size for a BF16 shard (as for pact_shard). */
 int64_t pact_digest_slots_bf16(const pact_shard_bf16* s);

@@ -76,6 +76,10 @@ class _CShardBf16(ctypes.Structure):
     ]
 
 
+class _CWorkspaceState(ctypes.Structure):
+    _fields_ = [("stream", ctypes.c_uint64), ("clear", ctypes.c_uint32), ("odd", ctypes.c_uint32)]
+
+
 class _CArenaLayout(ctypes.Structure):
     _fields_ = [("pool_bytes", ctypes.c_uint64), ("spacing", ctypes.c_uint64), ("offset", ctypes.c_uint64 * 5)]
 
@@ -106,6 +110,12 @@ def _lib():
         lib.pact_adamw_commit_bf16.restype = ctypes.c_int
         lib.pact_shard_digest_bf16.argtypes = [PB]
         lib.pact_shard_digest_bf16.restype = ctypes.c_int
+        W, H, u64 = ctypes.POINTER(_CWorkspaceState), ctypes.POINTER(_CHyper), ctypes.c_uint64
+        for name, args in (("adamw_commit", [P, u64, H, ctypes.c_uint32]), ("grad_guard", [P, ctypes.c_void_p]),
+                           ("shard_digest", [P]), ("bf16_digest", [P, ctypes.c_void_p]),
+                           ("adamw_commit_bf16", [PB, u64, H]), ("shard_digest_bf16", [PB])):
+            f = getattr(lib, f"pact_{name}_ws")
+            f.argtypes, f.restype = args + [W], ctypes.c_int
         lib.pact_digest_slots_bf16.argtypes = [PB]
         lib.pact_digest_slots_bf16.restype = ctypes.c_int64
         lib.pact_workspace_bytes_bf16.argtypes = [PB]
@@ -167,7 +177,31 @@ def _dev_tensor(t: Optional[torch.Tensor], dtype, name: str, n: int, device: Opt
     return t
 
 
-class Shard:
+class _Workspace:
+    """The digest workspace of a shard and what is known about it between
+    calls (``pact_workspace_state``): the library skips clearing a workspace
+    that its last call, on the same stream, left clear."""
+
+    def _init_workspace(self, nbytes: Optional[int]) -> None:
+        self.workspace = None
+        self._ws_state = _CWorkspaceState()
+        if nbytes is not None:
+            self.workspace = torch.zeros(nbytes, dtype=torch.uint8, device=self.device)
+            self._ws_state.stream = torch.cuda.current_stream(self.device).cuda_stream or 0
+            self._ws_state.clear = 1
+
+    @property
+    def workspace_clean(self) -> bool:
+        """Whether the workspace is clear for the next call; set False after
+        writing to it by other means."""
+        return bool(self._ws_state.clear)
+
+    @workspace_clean.setter
+    def workspace_clean(self, value: bool) -> None:
+        self._ws_state.clear = 1 if value else 0
+
+
+class Shard(_Workspace):
     """One rank's flat shard: fp32 param/grad/exp_avg/exp_avg_sq, a bf16 copy,
     and the device slots the digests land in.
 
@@ -204,16 +238,9 @@ class Shard:
         else:
             self._csegs = None
             self._chypers = None
-        # digest workspace: lets the partial sums spread over several addresses.
-        # Allocated zero-filled; every successful call leaves it so, which lets
-        # commits skip clearing it (workspace_clean stays true until a launch
-        # fails).
-        self.workspace = None
-        self.workspace_clean = False
-        if use_workspace:
-            nbytes = int(_lib().pact_workspace_bytes(ctypes.byref(self._c())))
-            self.workspace = torch.zeros(nbytes, dtype=torch.uint8, device=self.device)
-            self.workspace_clean = True
+        # digest workspace: lets the partial sums spread over several addresses
+        # and the last tile write the result
+        self._init_workspace(int(_lib().pact_workspace_bytes(ctypes.byref(self._c()))) if use_workspace else None)
 
     def _c(self, digest_out: Optional[torch.Tensor] = None, workspace: bool = True) -> _CShard:
         def ptr(t):
@@ -236,7 +263,7 @@ class Shard:
         return s
 
 
-class ShardBf16:
+class ShardBf16(_Workspace):
     """One rank's flat shard held in BF16 (the paper's precision for weights
     and moments): param, grad, exp_avg, exp_avg_sq as int16/bfloat16 tensors
     of bf16 bit patterns, and the digest slots.  Segments as for Shard."""
@@ -266,10 +293,7 @@ class ShardBf16:
         else:
             self._csegs = None
             self._chypers = None
-        self.workspace = None
-        if use_workspace:
-            nbytes = int(_lib().pact_workspace_bytes_bf16(ctypes.byref(self._c())))
-            self.workspace = torch.zeros(nbytes, dtype=torch.uint8, device=self.device)
+        self._init_workspace(int(_lib().pact_workspace_bytes_bf16(ctypes.byref(self._c()))) if use_workspace else None)
 
     def _c(self) -> _CShardBf16:
         def ptr(t):
@@ -372,16 +396,6 @@ PACT_COMMIT_ZERO_GRAD = 1
 PACT_COMMIT_WORKSPACE_CLEAN = 2
 
 
-def _note_workspace(shard, rc: int) -> None:
-    """After a failed launch the workspace may hold partial sums: stop
-    vouching that it is clear (the next commit clears it, and the call after
-    that may skip the clearing again)."""
-    if rc == PACT_EHIP:
-        shard.workspace_clean = False
-    elif rc == PACT_OK and getattr(shard, "workspace", None) is not None:
-        shard.workspace_clean = True
-
-
 def adamw_commit(shard: Shard, step: int, hyper: Optional[Hyper] = None, zero_grad: bool = False) -> torch.Tensor:
     """Commit one AdamW step on the shard (in place) and digest the result;
     with ``zero_grad`` the same pass also writes +0.0 into the gradient.
@@ -393,13 +407,11 @@ def adamw_commit(shard: Shard, step: int, hyper: Optional[Hyper] = None, zero_gr
         hyper = Hyper()
     ch = hyper._c() if hyper is not None else None
     flags = PACT_COMMIT_ZERO_GRAD if zero_grad else 0
-    if shard.workspace is not None and shard.workspace_clean:
-        flags |= PACT_COMMIT_WORKSPACE_CLEAN
     with torch.cuda.device(shard.device):
-        rc = _lib().pact_adamw_commit_ex(ctypes.byref(shard._c()), int(step),
-                                         ctypes.byref(ch) if ch is not None else None, flags)
-    _note_workspace(shard, rc)
-    _call("pact_adamw_commit_ex", rc)
+        rc = _lib().pact_adamw_commit_ws(ctypes.byref(shard._c()), int(step),
+                                         ctypes.byref(ch) if ch is not None else None, flags,
+                                         ctypes.byref(shard._ws_state))
+    _call("pact_adamw_commit_ws", rc)
     return shard.digest
 
 
@@ -426,26 +438,27 @@ def adamw_commit_bf16(shard: ShardBf16, step: int, hyper: Optional[Hyper] = None
         hyper = Hyper()
     ch = hyper._c() if hyper is not None else None
     with torch.cuda.device(shard.device):
-        rc = _lib().pact_adamw_commit_bf16(ctypes.byref(shard._c()), int(step),
-                                           ctypes.byref(ch) if ch is not None else None)
-    _call("pact_adamw_commit_bf16", rc)
+        rc = _lib().pact_adamw_commit_bf16_ws(ctypes.byref(shard._c()), int(step),
+                                              ctypes.byref(ch) if ch is not None else None,
+                                              ctypes.byref(shard._ws_state))
+    _call("pact_adamw_commit_bf16_ws", rc)
     return shard.digest
 
 
 def shard_digest_bf16(shard: ShardBf16) -> torch.Tensor:
     """Digest of the current BF16 (param, exp_avg, exp_avg_sq)."""
     with torch.cuda.device(shard.device):
-        rc = _lib().pact_shard_digest_bf16(ctypes.byref(shard._c()))
-    _call("pact_shard_digest_bf16", rc)
+        rc = _lib().pact_shard_digest_bf16_ws(ctypes.byref(shard._c()), ctypes.byref(shard._ws_state))
+    _call("pact_shard_digest_bf16_ws", rc)
     return shard.digest
 
 
 def _result_slots(shard, out: Optional[torch.Tensor]) -> torch.Tensor:
     """``out`` checked as a destination for the shard's result slots (int64
     device tensor on the shard's GPU, contiguous, at least ``shard.slots``
-    long), or a fresh zeroed one."""
+    long), or a fresh one (a call writes every slot)."""
     if out is None:
-        return torch.zeros(shard.slots, dtype=torch.int64, device=shard.device)
+        return torch.empty(shard.slots, dtype=torch.int64, device=shard.device)
     if not isinstance(out, torch.Tensor) or out.dtype != torch.int64:
         raise TypeError("out must be an int64 torch tensor")
     if out.device != shard.device:
@@ -459,18 +472,16 @@ def grad_guard(shard: Shard, out: Optional[torch.Tensor] = None) -> torch.Tensor
     """Count the gradient elements that are not +0.0 (per segment and total)."""
     out = _result_slots(shard, out)
     with torch.cuda.device(shard.device):
-        rc = _lib().pact_grad_guard(ctypes.byref(shard._c()), out.data_ptr())
-    _note_workspace(shard, rc)
-    _call("pact_grad_guard", rc)
+        rc = _lib().pact_grad_guard_ws(ctypes.byref(shard._c()), out.data_ptr(), ctypes.byref(shard._ws_state))
+    _call("pact_grad_guard_ws", rc)
     return out
 
 
 def shard_digest(shard: Shard) -> torch.Tensor:
     """Digest of the shard's current (param, exp_avg, exp_avg_sq)."""
     with torch.cuda.device(shard.device):
-        rc = _lib().pact_shard_digest(ctypes.byref(shard._c()))
-    _note_workspace(shard, rc)
-    _call("pact_shard_digest", rc)
+        rc = _lib().pact_shard_digest_ws(ctypes.byref(shard._c()), ctypes.byref(shard._ws_state))
+    _call("pact_shard_digest_ws", rc)
     return shard.digest
 
 
@@ -478,9 +489,8 @@ def bf16_digest(shard: Shard, out: Optional[torch.Tensor] = None) -> torch.Tenso
     """Digest (tag 3) of the bf16 copy, into ``out`` (allocated if None)."""
     out = _result_slots(shard, out)
     with torch.cuda.device(shard.device):
-        rc = _lib().pact_bf16_digest(ctypes.byref(shard._c()), out.data_ptr())
-    _note_workspace(shard, rc)
-    _call("pact_bf16_digest", rc)
+        rc = _lib().pact_bf16_digest_ws(ctypes.byref(shard._c()), out.data_ptr(), ctypes.byref(shard._ws_state))
+    _call("pact_bf16_digest_ws", rc)
     return out
 
 

@@ -13,21 +13,20 @@
 // ragged tail or a misaligned segment goes element by element.
 //
 // The digest is accumulated per thread in a 64-bit register (wrapping add),
-// summed over the workgroup with 64-bit LDS atomics (one word per wave, the
-// four words added by thread 0), and added with one 64-bit atomic per
-// workgroup into one of kLanes workspace words of its result slot (256 bytes
-// apart, so the atomics of neighbouring workgroups do not queue on one
-// address); a final
-// one-workgroup kernel sums the lanes and sets them back to zero, so a call
-// that is told its workspace is clear can skip clearing it.  Without a
-// workspace the atomics go to the result slot itself.  Wrapping addition is
-// associative and commutative, so the order in which workgroups arrive
-// cannot change the result.
+// summed over the workgroup with 64-bit LDS atomics (one word per wave), and
+// handed in with two 64-bit atomics per workgroup and result; the workgroup that hands in
+// the last share of a result slot writes the slot (see "result slots" below),
+// so a call is its tile launches alone.  Without a workspace each workgroup
+// adds its share to the result slot itself, which a launch before the tiles
+// clears.  Wrapping addition is associative and commutative, so the order in
+// which workgroups arrive cannot change the result.
 //
 // Arithmetic is the library contract in pactshard.h: one IEEE binary32
 // rounding per operation, no contraction or reassociation (the translation
 // unit is built with -ffp-contract=off and without fast-math), correctly
 // rounded sqrt and division, fp32 denormals kept.
+#include <algorithm>
+
 #include "launch.h"
 
 
@@ -404,6 +403,110 @@ __device__ __forceinline__ uint64_t block_sum(uint64_t x, uint64_t* lds) {
 }
 
 // ---------------------------------------------------------------------------
+// result slots: handing in the workgroups' shares
+//
+// A node is two workspace words that gather n shares x < 2^64:
+//   word 0  count in bits 44..63, sum of the shares' low 24 bits below it;
+//   word 1  sum of the high 40 bits in bits 24..63, count below it.
+// Each share is added with one relaxed atomic per word.  A word carries its
+// own count, so the arrival that finds n - 1 others there holds the word's
+// complete sum: it needs no ordering between different words, hence no fence
+// (at agent scope a release or acquire writes back or invalidates the XCD's
+// L2).  n <= 2^20 fits: 2^20 sums of 24 bits stay below 2^44, the high sum is
+// needed mod 2^40 only and drops off the top, and so may the low word's count
+// on its last arrival.  The last arrival at word 0 passes the carry out of 24
+// bits on to word 1, which therefore waits for n + 1 arrivals; the last
+// arrival at each word sets it back to zero and writes its bytes of the result
+// (3 and 5 of them: no thread ever holds all 64 bits beside a count).
+//
+// A result slot has one node its tiles arrive at when they are few, else
+// kLanes of them (256 bytes apart, so that neighbouring workgroups do not queue
+// on one address) whose last arrivals go on to the slot's own node; there the
+// count of word 0 sits in bits 56..63, since a lane's sum has up to 44 bits.
+// With per-segment results the tiles also arrive at the nodes of the total,
+// in the same instructions.
+//
+// There are two sets of nodes.  A call uses one and clears the other one
+// (which is clear already unless the caller broke its word about the
+// workspace), so that a caller who alternates them has right digests again one
+// call after a wrong one.
+//
+// Against a launch that sums the lanes behind the tiles, the last workgroup's
+// two or three dependent atomics take about 0.6 us each where that launch took
+// 2-3 us of the GPU and 2.5 us of the host.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kLowBits = 24;
+constexpr uint64_t kLowMask = (1ull << kLowBits) - 1;
+constexpr int kCountAtTiles = 44;  // where word 0's count begins in a node fed by tiles
+constexpr int kCountAtLanes = 56;  // and in one fed by lanes
+
+// Tiles of a result from which on its shares are spread over kLanes nodes: one
+// address takes about 11 ns per atomic, the further level 0.6 us once.
+constexpr uint32_t kSpreadTiles = 64;
+
+__device__ __forceinline__ uint64_t node_add(uint64_t* word, uint64_t x) {
+    return __hip_atomic_fetch_add(word, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void node_clear(uint64_t* word) {
+    __hip_atomic_store(word, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One tile hands in its share s to the result at dst, as number `index` of the
+// result's n tiles: one thread for word 0 and one for word 1, in the same
+// instructions.  Lane l's node is at lanes + l * kLaneStride.  (A wait for an
+// atomic's result waits for the stores before it too, so every store is issued
+// behind the next atomic.)
+__device__ __forceinline__ void hand_in(uint64_t* lanes, uint64_t* own, uint64_t* dst, uint32_t n, uint32_t index,
+                                        bool low, uint64_t s) {
+    const bool spread = n > kSpreadTiles;
+    const uint32_t l = index & (kLanes - 1);
+    const uint32_t word = low ? 0u : 1u;
+    uint64_t* const first = (spread ? lanes + l * kLaneStride : own) + word;
+    const uint32_t in_first = spread ? (n - l + kLanes - 1) / kLanes : n;  // the tiles that arrive there
+    const uint32_t in_own = spread ? (uint32_t)kLanes : n;
+    uint64_t part = low ? s & kLowMask : s & ~kLowMask;
+    uint64_t old = node_add(first, part + (low ? 1ull << kCountAtTiles : 1ull));
+    // word 1 of the own node gets word 0's carry besides
+    if ((low ? (uint32_t)(old >> kCountAtTiles) + 1u
+             : (uint32_t)(old & kLowMask) + (spread ? 1u : 0u)) != in_first) {
+        return;
+    }
+    part += low ? old & ((1ull << kCountAtTiles) - 1) : old & ~kLowMask;
+    if (spread) {
+        old = node_add(own + word, part + (low ? 1ull << kCountAtLanes : 1ull));
+        node_clear(first);
+        if ((low ? (uint32_t)(old >> kCountAtLanes) + 1u : (uint32_t)(old & kLowMask)) != in_own) return;
+        part += low ? old & ((1ull << kCountAtLanes) - 1) : old & ~kLowMask;
+    }
+    if (low) {
+        const uint64_t carry = part & ~kLowMask;
+        old = node_add(own + 1, carry + 1u);
+        node_clear(own);
+        uint8_t* const b = reinterpret_cast<uint8_t*>(dst);
+        *reinterpret_cast<uint16_t*>(b) = (uint16_t)part;
+        b[2] = (uint8_t)(part >> 16);
+        if ((uint32_t)(old & kLowMask) != in_own) return;
+        part = (old & ~kLowMask) + carry;
+    }
+    node_clear(own + 1);
+    uint8_t* const b = reinterpret_cast<uint8_t*>(dst);
+    b[3] = (uint8_t)(part >> kLowBits);
+    *reinterpret_cast<uint32_t*>(b + 4) = (uint32_t)(part >> 32);
+}
+
+// The nodes of a slot (of the total too, with slot 0) in the set that this
+// call does not use.
+__device__ __forceinline__ void clear_other_set(const Results& r, uint32_t slot) {
+    constexpr uint32_t kNodes = kNodesPerLane / 2;
+    if (threadIdx.x < kLanes * kNodes) {
+        uint64_t* node = r.words + ((uint64_t)slot * kLanes + threadIdx.x / kNodes) * kLaneStride +
+                         threadIdx.x % kNodes * 4 + (r.set ^ 1u) * 2;
+        node_clear(node);
+        node_clear(node + 1);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // HBM access: raw buffer instructions on a per-tile resource (base address in
 // scalar registers, 32-bit byte offset per lane), with the non-temporal cache
 // policy on loads and stores -- every byte is touched exactly once.
@@ -726,20 +829,35 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
     // Workgroup sum: every lane adds its share into its wave's LDS word with
     // one 64-bit LDS atomic (no VALU work: a shuffle tree costs about fifty
     // VALU instructions per lane, a few percent of a digesting kernel), then
-    // thread 0 adds the four words.
+    // the threads that hand it in add the four words.
     __hip_atomic_fetch_add(wave_sum, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __syncthreads();
-    uint64_t s = 0;
-    if (threadIdx.x == 0) {
+    const uint32_t slot = bt.per_segment ? bt.slot0 + seg : 0;
+    const uint32_t in_seg = (uint32_t)(tile - bt.tile_begin[seg]);
+    if (threadIdx.x < 4) {
+        uint64_t s = 0;
 #pragma unroll
         for (int w = 0; w < kBlock / 64; ++w) {
             s += lds[w];
         }
+        if (a.res.words == nullptr) {
+            if (threadIdx.x == 0 && s != 0) {
+                atomicAdd(reinterpret_cast<unsigned long long*>(a.res.digest + slot), (unsigned long long)s);
+            }
+        } else if (threadIdx.x < 2 || a.res.total_tiles != 0) {
+            // threads 0 and 1 for the slot, 2 and 3 for the total, whose nodes
+            // sit beside slot 0's
+            const bool total = threadIdx.x >= 2;
+            const uint32_t n = (uint32_t)(bt.tile_begin[seg + 1] - bt.tile_begin[seg]);
+            uint64_t* const line0 = a.res.words + a.res.set * 2;
+            uint64_t* const line = line0 + (uint64_t)slot * kLanes * kLaneStride;
+            hand_in(total ? line0 + 8 : line, total ? line0 + kLaneStride + 4 : line + 4,
+                    a.res.digest + (total ? a.res.total_slot : slot), total ? a.res.total_tiles : n,
+                    total ? bt.tile0 + (uint32_t)tile : in_seg, (threadIdx.x & 1) == 0, s);
+        }
     }
-    if (threadIdx.x == 0 && s != 0) {
-        const uint64_t r = bt.per_segment ? bt.slot0 + seg : 0;
-        uint64_t* dst = a.lanes ? a.lanes + (r * kLanes + (blockIdx.x & (kLanes - 1))) * kLaneStride : a.digest + r;
-        atomicAdd(reinterpret_cast<unsigned long long*>(dst), (unsigned long long)s);
+    if (a.res.words != nullptr && in_seg == 0) {
+        clear_other_set(a.res, slot);
     }
 }
 
@@ -768,48 +886,38 @@ void tile_kernel_bf16(ArraysBf16 a, Batch bt) {
     tile_body<M>(a, bt, lds);
 }
 
-__global__ __launch_bounds__(kBlock) void clear_kernel(uint64_t* digest, uint64_t* lanes, uint32_t nres,
+// Clears what the tile kernels hand their shares in to: every node of both
+// sets of the workspace when there is one, else the nslots result slots.
+__global__ __launch_bounds__(kBlock) void clear_kernel(uint64_t* digest, uint64_t* words, uint32_t nres,
                                                        uint32_t nslots) {
-    if (lanes) {
-        const uint32_t n = nres * kLanes;
-        for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
-            lanes[(uint64_t)i * kLaneStride] = 0;
+    const uint64_t stride = (uint64_t)gridDim.x * kBlock;
+    const uint64_t at = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (words) {
+        const uint64_t n = (uint64_t)nres * kLanes * kNodesPerLane;
+        for (uint64_t i = at; i < n; i += stride) {
+            uint64_t* node = words + (i / kNodesPerLane) * kLaneStride + (i % kNodesPerLane) * 2;
+            node[0] = 0;
+            node[1] = 0;
         }
     } else {
-        for (uint32_t i = threadIdx.x; i < nslots; i += kBlock) {
+        for (uint64_t i = at; i < nslots; i += stride) {
             digest[i] = 0;
         }
     }
 }
 
-// digest[r] = sum of r's lanes for r < nres (when lanes are used); with
-// per-segment results also digest[nres] = sum of digest[0..nres).  Each lane
-// is set back to zero once read, so a call always leaves its workspace lanes
-// at zero and the next call may skip clearing them.
-__global__ __launch_bounds__(kBlock) void finish_kernel(uint64_t* digest, uint64_t* lanes, uint32_t nres,
-                                                        uint32_t per_segment) {
+// digest[nres] = sum of digest[0..nres): the total of per-segment results
+// where the tile kernels do not form it (no workspace, or more segments than
+// a node counts).
+__global__ __launch_bounds__(kBlock) void total_kernel(uint64_t* digest, uint32_t nres) {
     __shared__ uint64_t lds[kBlock / 64];
     uint64_t total = 0;
     for (uint32_t r = threadIdx.x; r < nres; r += kBlock) {
-        uint64_t x;
-        if (lanes) {
-            x = 0;
-            for (int l = 0; l < kLanes; ++l) {
-                uint64_t* lane = lanes + ((uint64_t)r * kLanes + l) * kLaneStride;
-                x += *lane;
-                *lane = 0;
-            }
-            digest[r] = x;
-        } else {
-            x = digest[r];
-        }
-        total += x;
+        total += digest[r];
     }
-    if (per_segment) {
-        const uint64_t t = block_sum(total, lds);
-        if (threadIdx.x == 0) {
-            digest[nres] = t;
-        }
+    const uint64_t t = block_sum(total, lds);
+    if (threadIdx.x == 0) {
+        digest[nres] = t;
     }
 }
 
@@ -877,8 +985,10 @@ __global__ __launch_bounds__(kBlock) void probe_persistent_kernel(const float* i
 
 }  // namespace
 
-hipError_t launch_clear(uint64_t* digest, uint64_t* lanes, uint32_t nres, uint32_t nslots, hipStream_t stream) {
-    hipLaunchKernelGGL(clear_kernel, dim3(1), dim3(kBlock), 0, stream, digest, lanes, nres, nslots);
+hipError_t launch_clear(uint64_t* digest, uint64_t* words, uint32_t nres, uint32_t nslots, hipStream_t stream) {
+    const uint64_t n = words ? (uint64_t)nres * kLanes * kNodesPerLane : nslots;
+    const uint32_t grid = (uint32_t)std::min<uint64_t>((n + kBlock - 1) / kBlock, 1024);
+    hipLaunchKernelGGL(clear_kernel, dim3(grid), dim3(kBlock), 0, stream, digest, words, nres, nslots);
     return hipGetLastError();
 }
 
@@ -919,8 +1029,8 @@ hipError_t launch_batch_bf16(Mode mode, const ArraysBf16& a, const Batch& b, uin
     return hipGetLastError();
 }
 
-hipError_t launch_finish(uint64_t* digest, uint64_t* lanes, uint32_t nres, bool per_segment, hipStream_t stream) {
-    hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(kBlock), 0, stream, digest, lanes, nres, per_segment ? 1u : 0u);
+hipError_t launch_total(uint64_t* digest, uint32_t nres, hipStream_t stream) {
+    hipLaunchKernelGGL(total_kernel, dim3(1), dim3(kBlock), 0, stream, digest, nres);
     return hipGetLastError();
 }
 

@@ -19,10 +19,25 @@ constexpr int kVec = 4;
 constexpr int kUnroll = 4;
 constexpr int kTile = kBlock * kVec * kUnroll;  // 4096 elements per tile
 
-// Digest partial sums: each result slot owns kLanes workspace words,
-// kLaneStride words (256 bytes) apart; workgroup w adds into lane w % kLanes.
+// Digest partial sums: each result slot owns kLanes workspace lines of
+// kLaneStride words (256 bytes); a line begins with kNodesPerLane nodes of two
+// words: two sets each of a lane's node, of a slot's own (in lane 0's line; the
+// total's in lane 1's of slot 0) and of the total's lanes (of slot 0).
 constexpr int kLanes = 16;
 constexpr int kLaneStride = 32;
+constexpr int kNodesPerLane = 6;
+
+// Tiles whose arrivals the nodes of one result can count: 2^20 per lane.
+constexpr uint64_t kGatherTiles = (uint64_t)kLanes << 20;
+
+// Where the tiles' shares go.
+struct Results {
+    uint64_t* digest;      // result slots
+    uint64_t* words;       // the workspace, or null: shares are added to the result slots
+    uint32_t set;          // which set of nodes the call uses (0 or 1)
+    uint32_t total_slot;   // the slot of the per-segment results' sum
+    uint32_t total_tiles;  // the call's tiles, which also gather into total_slot; 0: they do not
+};
 
 // Per-segment binary32 scalars of one step.
 struct StepScalars {
@@ -30,10 +45,12 @@ struct StepScalars {
 };
 
 // One launch's slice of the segment table.  Tiles never straddle segments:
-// segment s owns tiles [tile_begin[s], tile_begin[s+1]).
+// segment s owns tiles [tile_begin[s], tile_begin[s+1]), at
+// least one (an empty segment's tile hands in a share of zero).
 struct Batch {
     uint32_t nseg;
     uint32_t slot0;        // result slot of this batch's first segment
+    uint32_t tile0;        // tiles of the call's earlier batches
     uint32_t per_segment;  // nonzero: one result slot per segment, else one in all
     uint64_t tile_begin[kSegsPerLaunch + 1];
     uint64_t elem_begin[kSegsPerLaunch];  // shard-relative first element
@@ -50,8 +67,7 @@ struct Arrays {
     float* v;
     uint16_t* b;
     uint64_t goff;      // global flat index of shard element 0
-    uint64_t* digest;   // result slots
-    uint64_t* lanes;    // workspace lanes, or null: atomics go to the result slots
+    Results res;
 };
 
 // The same arrays for a shard held in BF16 (no separate working copy).
@@ -61,8 +77,7 @@ struct ArraysBf16 {
     uint16_t* m;
     uint16_t* v;
     uint64_t goff;
-    uint64_t* digest;
-    uint64_t* lanes;
+    Results res;
 };
 
 enum class Mode : int {
@@ -75,9 +90,9 @@ enum class Mode : int {
     DigestBf16State = 6,
 };
 
-// Enqueue the clearing of what the tile kernels accumulate into: the
-// nres * kLanes lane words when `lanes` is given, else the nslots digest slots.
-hipError_t launch_clear(uint64_t* digest, uint64_t* lanes, uint32_t nres, uint32_t nslots, hipStream_t stream);
+// Enqueue the clearing of what the tile kernels hand their shares in to: the
+// nodes of nres result slots when `words` is given, else the nslots digest slots.
+hipError_t launch_clear(uint64_t* digest, uint64_t* words, uint32_t nres, uint32_t nslots, hipStream_t stream);
 
 // Enqueue one batch in the given mode: one workgroup per tile, so `grid` is
 // the batch's tile count.
@@ -86,9 +101,8 @@ hipError_t launch_batch(Mode mode, const Arrays& a, const Batch& b, uint32_t gri
 // Enqueue one batch of a BF16-state mode (CommitBf16State, DigestBf16State).
 hipError_t launch_batch_bf16(Mode mode, const ArraysBf16& a, const Batch& b, uint32_t grid, hipStream_t stream);
 
-// Enqueue the final sums: digest[r] = sum of r's lanes (when `lanes` is
-// given) for r < nres, and, with per-segment results, digest[nres] = their sum.
-hipError_t launch_finish(uint64_t* digest, uint64_t* lanes, uint32_t nres, bool per_segment, hipStream_t stream);
+// Enqueue digest[nres] = sum of digest[0..nres).
+hipError_t launch_total(uint64_t* digest, uint32_t nres, hipStream_t stream);
 
 // Enqueue the 30-byte/element stream probe (n a multiple of kVec): one
 // workgroup per tile when workgroups == 0, else a persistent grid of that

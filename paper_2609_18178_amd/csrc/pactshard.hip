@@ -15,8 +15,12 @@ static_assert(pact::kBlock % 64 == 0 && pact::kBlock <= 1024, "whole waves of 64
 static_assert(pact::kVec == 4, "the binary32 vector path moves 16-byte vectors of four elements");
 static_assert(pact::kTile % (pact::kBlock * 8) == 0,
               "a BF16-state tile is whole rows of 16-byte vectors of eight elements");
-static_assert((pact::kLanes & (pact::kLanes - 1)) == 0, "lane = workgroup & (kLanes - 1)");
+static_assert((pact::kLanes & (pact::kLanes - 1)) == 0, "lane = tile & (kLanes - 1)");
+static_assert(pact::kLanes >= 2, "the total's node sits beside lane 1's");
 static_assert(pact::kLaneStride * sizeof(uint64_t) >= 128, "lanes sit in separate cache lines");
+static_assert(pact::kNodesPerLane * 2 <= pact::kLaneStride, "a lane's nodes fit its line");
+static_assert(UINT32_MAX / pact::kBlock <= pact::kGatherTiles, "a result's nodes count the tiles of a launch");
+static_assert(pact::kNodesPerLane == 6 && pact::kLanes * 3 <= pact::kBlock, "clear_other_set: a thread per node");
 static_assert((uint64_t)pact::kTile * 4 <= (1ull << 31), "a tile's byte offsets fit the 32-bit buffer offset");
 static_assert(pact::kSegsPerLaunch >= 1, "a launch takes at least one segment");
 
@@ -26,6 +30,9 @@ thread_local int g_last_hip_error = 0;
 
 constexpr uint64_t kIndexLimit = 1ull << 56;  // indices must stay below the tag bits
 constexpr uint32_t kMaxSegments = 1u << 24;     // keeps every slot and lane index in 32 bits
+// A dispatch counts its work-items in 32 bits, so one launch holds at most
+// this many tiles.
+constexpr uint64_t kMaxTiles = UINT32_MAX / pact::kBlock;
 
 int fail_hip(hipError_t e) {
     g_last_hip_error = static_cast<int>(e);
@@ -157,9 +164,7 @@ int validate(const View& s, const Uses& use, const uint64_t* out, uint64_t* nslo
             tiles += (sg.length + pact::kTile - 1) / pact::kTile;  // tiles never straddle segments
         }
     }
-    // A dispatch counts its work-items in 32 bits, so one launch holds at most
-    // UINT32_MAX / kBlock tiles; the total bounds every launch's share.
-    if (tiles > (uint64_t)(UINT32_MAX / pact::kBlock)) return PACT_ERANGE;
+    if (tiles > kMaxTiles) return PACT_ERANGE;  // the total bounds every launch's share
     if (!aligned(out, 8)) return PACT_EALIGN;
     for (int k = 0; k < kSlots; ++k) {
         if (use.slot[k] && !aligned(s.arr[k], s.esize[k])) return PACT_EALIGN;
@@ -283,7 +288,7 @@ struct SegSource {
     uint64_t step;
     bool need_hyper;
 
-    size_t count() const { return s->segs ? (size_t)s->num_segs : (s->numel > 0 ? 1 : 0); }
+    size_t count() const { return s->segs ? (size_t)s->num_segs : 1; }
     SegWork at(size_t k) const {
         SegWork w{0, s->numel, {}};
         const pact_hyper* h = single;
@@ -336,16 +341,37 @@ bool vector_ok(pact::Mode mode, const View& s, uint64_t first) {
     return false;
 }
 
-// workspace_clean: the caller vouches that the workspace lanes are zero (the
-// finish kernel leaves them so), and the clearing launch is skipped.
-int run(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, uint64_t nslots,
-        bool workspace_clean = false) {
+// Tiles of a segment.  An empty one (an empty shard too) has one: it is the
+// tiles that write the result slots.
+uint64_t tiles_of(uint64_t count) { return std::max<uint64_t>(1, (count + pact::kTile - 1) / pact::kTile); }
+
+// What the caller says about the workspace: clean = every node is zero (the
+// tile kernels leave them so), and the clearing launch is skipped; odd = the
+// call uses the second set of nodes.
+struct Workspace {
+    bool clean = false;
+    bool odd = false;
+};
+
+int run(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, uint64_t nslots, Workspace ws) {
     hipStream_t stream = static_cast<hipStream_t>(s.stream);
-    uint64_t* lanes = static_cast<uint64_t*>(s.workspace);
     const uint32_t nres = (uint32_t)result_slots(s);
+    const bool per_segment = s.segs != nullptr;
+    pact::Results res;
+    res.digest = out;
+    res.words = static_cast<uint64_t*>(s.workspace);
+    res.set = ws.odd ? 1u : 0u;
+    res.total_slot = nres;
+    res.total_tiles = 0;
+    const size_t nwork = work.count();
+    if (per_segment && res.words != nullptr) {
+        uint64_t all = 0;
+        for (size_t k = 0; k < nwork; ++k) all += tiles_of(s.segs[k].length);
+        if (all <= pact::kGatherTiles) res.total_tiles = (uint32_t)all;
+    }
     hipError_t e = hipSuccess;
-    if (!(workspace_clean && lanes != nullptr)) {
-        e = pact::launch_clear(out, lanes, nres, (uint32_t)nslots, stream);
+    if (!(ws.clean && res.words != nullptr)) {
+        e = pact::launch_clear(out, res.words, nres, (uint32_t)nslots, stream);
         if (e != hipSuccess) return fail_hip(e);
     }
 
@@ -359,8 +385,7 @@ int run(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, ui
         ab.m = static_cast<uint16_t*>(const_cast<void*>(s.arr[kM]));
         ab.v = static_cast<uint16_t*>(const_cast<void*>(s.arr[kV]));
         ab.goff = s.goff;
-        ab.digest = out;
-        ab.lanes = lanes;
+        ab.res = res;
     } else {
         a.p = static_cast<float*>(const_cast<void*>(s.arr[kP]));
         a.g = static_cast<const float*>(s.arr[kG]);
@@ -369,44 +394,46 @@ int run(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, ui
         a.v = static_cast<float*>(const_cast<void*>(s.arr[kV]));
         a.b = static_cast<uint16_t*>(const_cast<void*>(s.arr[kB]));
         a.goff = s.goff;
-        a.digest = out;
-        a.lanes = lanes;
+        a.res = res;
     }
 
-    const bool per_segment = s.segs != nullptr;
-    const size_t nwork = work.count();
-    for (size_t first = 0; first < nwork; first += pact::kSegsPerLaunch) {
-        const size_t cnt = std::min<size_t>(pact::kSegsPerLaunch, nwork - first);
+    uint64_t tile0 = 0;
+    for (size_t first = 0; first < nwork;) {
         pact::Batch b;
         std::memset(&b, 0, sizeof b);
-        b.nseg = (uint32_t)cnt;
         b.slot0 = (uint32_t)first;
+        b.tile0 = (uint32_t)tile0;
         b.per_segment = per_segment ? 1u : 0u;
         uint64_t tiles = 0;
-        for (size_t k = 0; k < cnt; ++k) {
-            const SegWork w = work.at(first + k);
-            b.tile_begin[k] = tiles;
-            tiles += (w.count + pact::kTile - 1) / pact::kTile;
-            b.elem_begin[k] = w.first;
-            b.elem_count[k] = w.count;
-            b.sc[k] = w.sc;
-            b.vec_ok[k] = vector_ok(mode, s, w.first) ? 1u : 0u;
+        size_t cnt = 0;
+        for (; cnt < (size_t)pact::kSegsPerLaunch && first + cnt < nwork; ++cnt) {
+            const SegWork w = work.at(first + cnt);
+            const uint64_t t = tiles_of(w.count);
+            if (tiles + t > kMaxTiles) break;
+            b.tile_begin[cnt] = tiles;
+            tiles += t;
+            b.elem_begin[cnt] = w.first;
+            b.elem_count[cnt] = w.count;
+            b.sc[cnt] = w.sc;
+            b.vec_ok[cnt] = vector_ok(mode, s, w.first) ? 1u : 0u;
         }
+        b.nseg = (uint32_t)cnt;
         b.tile_begin[cnt] = tiles;
-        if (tiles == 0) continue;
         e = is_bf16_state(mode) ? pact::launch_batch_bf16(mode, ab, b, (uint32_t)tiles, stream)
                                 : pact::launch_batch(mode, a, b, (uint32_t)tiles, stream);
         if (e != hipSuccess) return fail_hip(e);
+        first += cnt;
+        tile0 += tiles;
     }
-    if (lanes != nullptr || per_segment) {
-        e = pact::launch_finish(out, lanes, nres, per_segment, stream);
+    if (per_segment && res.total_tiles == 0) {
+        e = pact::launch_total(out, nres, stream);
         if (e != hipSuccess) return fail_hip(e);
     }
     return PACT_OK;
 }
 
 // ---------------------------------------------------------------------------
-// Static scratch of pact_adamw_commit_static: the digest lanes of up to
+// Static scratch of pact_adamw_commit_static: the digest nodes of up to
 // PACT_STATIC_MAX_SEGMENTS result slots in device memory the library holds
 // for the life of the process, one copy per GPU.  In host code `scratch`
 // names a host-side stand-in, not a device address: the device address of
@@ -454,10 +481,10 @@ int static_scratch_ptr(void* stream, void** out) {
 }
 
 // A commit mode: check step and hyperparameters, validate, enqueue.  With
-// static_scratch the digest lanes are the library's static array (the
-// caller's workspace must be absent).
-int commit(pact::Mode mode, View s, uint64_t step, const pact_hyper* hyper, const Uses& use,
-           bool workspace_clean = false, bool static_scratch = false) {
+// static_scratch the nodes are the library's static array (the caller's
+// workspace must be absent).
+int commit(pact::Mode mode, View s, uint64_t step, const pact_hyper* hyper, const Uses& use, Workspace ws,
+           bool static_scratch = false) {
     if (step == 0) return PACT_EINVAL;
     if (s.segs == nullptr && (hyper == nullptr || !hyper_ok(*hyper))) return PACT_EINVAL;
     uint64_t nslots = 0;
@@ -468,24 +495,61 @@ int commit(pact::Mode mode, View s, uint64_t step, const pact_hyper* hyper, cons
     if (static_scratch) {
         if (s.workspace != nullptr) return PACT_EINVAL;
         if (result_slots(s) > PACT_STATIC_MAX_SEGMENTS) return PACT_ESCRATCH;
-        void* lanes = nullptr;
-        rc = static_scratch_ptr(s.stream, &lanes);
+        void* words = nullptr;
+        rc = static_scratch_ptr(s.stream, &words);
         if (rc != PACT_OK) return rc;
-        s.workspace = lanes;
+        s.workspace = words;
         s.workspace_bytes = kStaticScratchBytes;
-        workspace_clean = false;  // shared by every call on the GPU: always cleared first
+        ws = Workspace{};  // shared by every call on the GPU: always cleared first
     }
     const SegSource work{&s, hyper, step, true};
-    return run(mode, s, work, s.digest, nslots, workspace_clean);
+    return run(mode, s, work, s.digest, nslots, ws);
 }
 
 // A mode that only reads the shard: validate, enqueue.
-int measure(pact::Mode mode, const View& s, const Uses& use, uint64_t* out) {
+int measure(pact::Mode mode, const View& s, const Uses& use, uint64_t* out, Workspace ws) {
     uint64_t nslots = 0;
     int rc = validate(s, use, out, &nslots);
     if (rc != PACT_OK) return rc;
     const SegSource work{&s, nullptr, 0, false};
-    return run(mode, s, work, out, nslots);
+    return run(mode, s, work, out, nslots, ws);
+}
+
+// What a call may take for granted of the workspace in the state `ws`.
+template <typename S>
+Workspace workspace_of(const S* s, const pact_workspace_state* ws) {
+    if (ws == nullptr) return {};
+    return {ws->clear != 0 && ws->stream == s->stream, (ws->odd & 1u) != 0};
+}
+
+// The state after a call that returned rc.  A call that was captured has not
+// run: it proves nothing about a workspace that was not known to be clear.
+template <typename S>
+int note_workspace(const S* s, pact_workspace_state* ws, int rc) {
+    if (ws == nullptr || s == nullptr) return rc;
+    if (rc == PACT_EHIP) {
+        ws->clear = 0;
+    } else if (rc == PACT_OK && s->workspace != nullptr) {
+        if (ws->clear == 0 && s->stream != nullptr) {
+            hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+            const hipError_t e = hipStreamIsCapturing(static_cast<hipStream_t>(s->stream), &status);
+            if (e != hipSuccess || status != hipStreamCaptureStatusNone) return rc;
+        }
+        ws->stream = s->stream;
+        ws->clear = 1;
+        ws->odd ^= 1u;
+    }
+    return rc;
+}
+
+constexpr Uses kUsesAll = {{true, true, true, true, true}};
+constexpr Uses kUsesState = {{true, false, true, true, false}};
+constexpr Uses kUsesGrad = {{false, true, false, false, false}};
+constexpr Uses kUsesCopy = {{false, false, false, false, true}};
+constexpr Uses kUsesAllBf16 = {{true, true, true, true, false}};
+
+pact::Mode commit_mode(uint32_t flags) {
+    return (flags & PACT_COMMIT_ZERO_GRAD) ? pact::Mode::CommitZeroGrad : pact::Mode::Commit;
 }
 
 }  // namespace
@@ -514,51 +578,68 @@ int64_t pact_workspace_bytes_bf16(const pact_shard_bf16* s) {
 
 int pact_adamw_commit_ex(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags) {
     if (s == nullptr || (flags & ~(PACT_COMMIT_ZERO_GRAD | PACT_COMMIT_WORKSPACE_CLEAN)) != 0) return PACT_EINVAL;
-    const Uses use = {{true, true, true, true, true}};
-    const pact::Mode mode = (flags & PACT_COMMIT_ZERO_GRAD) ? pact::Mode::CommitZeroGrad : pact::Mode::Commit;
-    return commit(mode, view_of(s), step, hyper, use, (flags & PACT_COMMIT_WORKSPACE_CLEAN) != 0);
+    return commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll,
+                  {(flags & PACT_COMMIT_WORKSPACE_CLEAN) != 0, false});
 }
 
 int pact_adamw_commit(const pact_shard* s, uint64_t step, const pact_hyper* hyper) {
     return pact_adamw_commit_ex(s, step, hyper, 0u);
 }
 
+int pact_adamw_commit_ws(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags,
+                         pact_workspace_state* ws) {
+    if (s == nullptr || (flags & ~PACT_COMMIT_ZERO_GRAD) != 0) return PACT_EINVAL;
+    return note_workspace(s, ws,
+                          commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll, workspace_of(s, ws)));
+}
+
 int pact_adamw_commit_static(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags) {
     if (s == nullptr || (flags & ~PACT_COMMIT_ZERO_GRAD) != 0) return PACT_EINVAL;
-    const Uses use = {{true, true, true, true, true}};
-    const pact::Mode mode = (flags & PACT_COMMIT_ZERO_GRAD) ? pact::Mode::CommitZeroGrad : pact::Mode::Commit;
-    return commit(mode, view_of(s), step, hyper, use, false, true);
+    return commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll, {}, true);
 }
 
-int pact_grad_guard(const pact_shard* s, uint64_t* dev_out) {
+int pact_grad_guard_ws(const pact_shard* s, uint64_t* dev_out, pact_workspace_state* ws) {
     if (s == nullptr) return PACT_EINVAL;
-    const Uses use = {{false, true, false, false, false}};
-    return measure(pact::Mode::GradGuard, view_of(s), use, dev_out);
+    return note_workspace(s, ws,
+                          measure(pact::Mode::GradGuard, view_of(s), kUsesGrad, dev_out, workspace_of(s, ws)));
 }
 
-int pact_shard_digest(const pact_shard* s) {
+int pact_grad_guard(const pact_shard* s, uint64_t* dev_out) { return pact_grad_guard_ws(s, dev_out, nullptr); }
+
+int pact_shard_digest_ws(const pact_shard* s, pact_workspace_state* ws) {
     if (s == nullptr) return PACT_EINVAL;
-    const Uses use = {{true, false, true, true, false}};
-    return measure(pact::Mode::StateDigest, view_of(s), use, s->digest_dev);
+    return note_workspace(
+        s, ws, measure(pact::Mode::StateDigest, view_of(s), kUsesState, s->digest_dev, workspace_of(s, ws)));
 }
 
-int pact_bf16_digest(const pact_shard* s, uint64_t* dev_out) {
+int pact_shard_digest(const pact_shard* s) { return pact_shard_digest_ws(s, nullptr); }
+
+int pact_bf16_digest_ws(const pact_shard* s, uint64_t* dev_out, pact_workspace_state* ws) {
     if (s == nullptr) return PACT_EINVAL;
-    const Uses use = {{false, false, false, false, true}};
-    return measure(pact::Mode::Bf16Digest, view_of(s), use, dev_out);
+    return note_workspace(s, ws,
+                          measure(pact::Mode::Bf16Digest, view_of(s), kUsesCopy, dev_out, workspace_of(s, ws)));
+}
+
+int pact_bf16_digest(const pact_shard* s, uint64_t* dev_out) { return pact_bf16_digest_ws(s, dev_out, nullptr); }
+
+int pact_adamw_commit_bf16_ws(const pact_shard_bf16* s, uint64_t step, const pact_hyper* hyper,
+                              pact_workspace_state* ws) {
+    if (s == nullptr) return PACT_EINVAL;
+    return note_workspace(
+        s, ws, commit(pact::Mode::CommitBf16State, view_of(s), step, hyper, kUsesAllBf16, workspace_of(s, ws)));
 }
 
 int pact_adamw_commit_bf16(const pact_shard_bf16* s, uint64_t step, const pact_hyper* hyper) {
-    if (s == nullptr) return PACT_EINVAL;
-    const Uses use = {{true, true, true, true, false}};
-    return commit(pact::Mode::CommitBf16State, view_of(s), step, hyper, use);
+    return pact_adamw_commit_bf16_ws(s, step, hyper, nullptr);
 }
 
-int pact_shard_digest_bf16(const pact_shard_bf16* s) {
+int pact_shard_digest_bf16_ws(const pact_shard_bf16* s, pact_workspace_state* ws) {
     if (s == nullptr) return PACT_EINVAL;
-    const Uses use = {{true, false, true, true, false}};
-    return measure(pact::Mode::DigestBf16State, view_of(s), use, s->digest_dev);
+    return note_workspace(
+        s, ws, measure(pact::Mode::DigestBf16State, view_of(s), kUsesState, s->digest_dev, workspace_of(s, ws)));
 }
+
+int pact_shard_digest_bf16(const pact_shard_bf16* s) { return pact_shard_digest_bf16_ws(s, nullptr); }
 
 int pact_arena_plan(uint64_t numel, uint64_t spacing, pact_arena_layout* out) {
     if (out == nullptr) return PACT_EINVAL;
@@ -588,7 +669,7 @@ int pact_stream_probe_grid(const float* in0, const float* in1, const float* in2,
         return PACT_EALIGN;
     }
     const uint64_t tiles = (n + pact::kTile - 1) / pact::kTile;
-    if (tiles > (uint64_t)(UINT32_MAX / pact::kBlock) || workgroups > UINT32_MAX / pact::kBlock) return PACT_ERANGE;
+    if (tiles > kMaxTiles || workgroups > kMaxTiles) return PACT_ERANGE;
     hipError_t e = pact::launch_probe(in0, in1, in2, in3, out0, out2, out3, out_half, n, workgroups,
                                       static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail_hip(e);
