@@ -35,9 +35,9 @@
  * read (and overwritten with +0.0 only by a commit asked to zero it);
  * param_bf16 is only written.  The five arrays must not overlap each
  * other or digest_dev.  fp32 arrays need 4-byte and bf16 2-byte alignment;
- * a segment whose start is 16-byte aligned in all four fp32 arrays and 8-byte
- * aligned in the bf16 array runs the vector path, any other segment the
- * element-wise path, with identical results.
+ * a segment runs the vector path from its first element on that is 16-byte
+ * aligned in all four fp32 arrays and 8-byte aligned in the bf16 array; one
+ * that has none runs the element-wise path, with identical results.
  *
  * Segments (at most 2^24).  segs == NULL: the shard is one segment [0, numel) updated with
  * *hyper, and digest_dev[0] receives D.  Otherwise segs[0..num_segs) lists
@@ -206,8 +206,8 @@ int pact_bf16_digest(const pact_shard* s, uint64_t* dev_out);
 /* One rank's flat shard held in BF16, the paper's own precision for weights
  * and AdamW moments (Sec. IV-A): the fields of pact_shard with 16-bit
  * arrays (bf16 bit patterns) and no separate working copy.  fp32 rules apply
- * with 2-byte alignment; a segment whose start is 16-byte aligned in all four
- * arrays runs the vector path. */
+ * with 2-byte alignment; a segment runs the vector path from its first element
+ * on that is 16-byte aligned in all four arrays. */
 typedef struct pact_shard_bf16 {
     uint16_t* param;          /* W, bf16, numel elements                       */
     const uint16_t* grad;     /* bf16 gradient                                 */

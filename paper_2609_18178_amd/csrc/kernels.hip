@@ -9,8 +9,11 @@
 // slower on this pattern).  A full, aligned tile moves, per thread and per
 // binary32 array, four 16-byte vectors with buffer_load/store_dwordx4, and four
 // 8-byte ones into the bf16 working copy (dwordx2); on BF16 state, two 16-byte
-// vectors of eight elements per array.  All of it is marked non-temporal; a
-// ragged tail or a misaligned segment goes element by element.
+// vectors of eight elements per array.  All of it is marked non-temporal.  A
+// segment's tiles begin at its first element that is aligned in every array
+// (up to seven elements in), and a last tile that is not full masks its
+// vectors; only the elements before the first and behind the last vector, and
+// segments whose arrays are never aligned together, go element by element.
 //
 // The digest is accumulated per thread in a 64-bit register (wrapping add),
 // summed over the workgroup with 64-bit LDS atomics (one word per wave), and
@@ -265,6 +268,12 @@ struct IndexLo16 {
         return mix_after_first_round(prod, lo1 * chi);
     }
 };
+
+// Elements of one vector of a tile.
+template <typename A>
+constexpr uint32_t kVecElems = kVec;
+template <>
+constexpr uint32_t kVecElems<ArraysBf16> = 8;
 
 // Whether the `count` indices from `first` on share their upper 32 bits.
 __device__ __forceinline__ bool same_high_half(uint64_t first, uint64_t count) {
@@ -578,78 +587,85 @@ __device__ __forceinline__ uint64_t do_scalar(const Arrays& a, uint64_t e, const
 }
 
 // ---------------------------------------------------------------------------
-// one full tile whose start is 16-byte aligned in every fp32 array (8-byte in
-// the bf16 array): kUnroll rows of kBlock 16-byte vectors per array.  Row u,
-// lane t holds elements e0 + u*kBlock*4 + 4t .. +3.
+// one tile whose start is 16-byte aligned in every fp32 array (8-byte in the
+// bf16 array): Rows rows of kBlock 16-byte vectors per array.  Row u, lane t
+// holds elements e0 + u*kBlock*4 + 4t .. +3.  Masked: one row of which only the
+// first nvec vectors exist; the buffer range check drops the others' loads and
+// stores (whole vectors, since the range ends with one), and their hashes are
+// not counted (and go one element after another: it is not to cost the full
+// tiles registers).
 // ---------------------------------------------------------------------------
-template <Mode M, typename Ix>
-__device__ __forceinline__ uint64_t do_tile_vec(const Arrays& a, uint64_t e0, const StepScalars& sc) {
+template <Mode M, typename Ix, int Rows, bool Masked>
+__device__ __forceinline__ uint64_t do_tile_vec(const Arrays& a, uint64_t e0, uint32_t nvec, const StepScalars& sc) {
     constexpr uint32_t kRow32 = kBlock * kVec * 4;  // bytes of one fp32 row
     constexpr uint32_t kRow16 = kBlock * kVec * 2;  // bytes of one bf16 row
+    static_assert(!Masked || Rows == 1, "a masked tile is one row");
+    const uint32_t bytes32 = Masked ? nvec * kVec * 4 : Rows * kRow32;
+    const uint32_t bytes16 = Masked ? nvec * kVec * 2 : Rows * kRow16;
     const uint32_t lane32 = threadIdx.x * kVec * 4;
     const uint32_t lane16 = threadIdx.x * kVec * 2;
     const Ix ix(a.goff + e0, threadIdx.x * kVec);  // word k of this lane: index + k
     uint64_t acc = 0;
     if constexpr (M == Mode::GradGuard) {
-        const auto rg = tile_rsrc(a.g + e0, kTile * 4);
-        u32x4 G[kUnroll];
+        const auto rg = tile_rsrc(a.g + e0, bytes32);
+        u32x4 G[Rows];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < Rows; ++u) {
             G[u] = load16(rg, lane32 + u * kRow32);
         }
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < Rows; ++u) {
 #pragma unroll
             for (int j = 0; j < kVec; ++j) {
-                acc += G[u][j] != 0u ? 1u : 0u;
+                acc += G[u][j] != 0u ? 1u : 0u;  // a dropped load reads zero
             }
         }
         return acc;
     } else if constexpr (M == Mode::Bf16Digest) {
-        const auto rb = tile_rsrc(a.b + e0, kTile * 2);
-        u32x2 W[kUnroll];
+        const auto rb = tile_rsrc(a.b + e0, bytes16);
+        u32x2 W[Rows];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < Rows; ++u) {
             W[u] = load8(rb, lane16 + u * kRow16);
         }
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < Rows; ++u) {
             const uint32_t o = u * kBlock * kVec;
             acc += ix.template hash<kTagB>(W[u].x & 0xFFFFu, o) + ix.template hash<kTagB>(W[u].x >> 16, o + 1) +
                    ix.template hash<kTagB>(W[u].y & 0xFFFFu, o + 2) + ix.template hash<kTagB>(W[u].y >> 16, o + 3);
         }
-        return acc;
+        return Masked && threadIdx.x >= nvec ? 0 : acc;
     } else {
-        const auto rp = tile_rsrc(a.p + e0, kTile * 4);
-        const auto rm = tile_rsrc(a.m + e0, kTile * 4);
-        const auto rv = tile_rsrc(a.v + e0, kTile * 4);
-        u32x4 P[kUnroll], G[kUnroll], Mo[kUnroll], V[kUnroll];
+        const auto rp = tile_rsrc(a.p + e0, bytes32);
+        const auto rm = tile_rsrc(a.m + e0, bytes32);
+        const auto rv = tile_rsrc(a.v + e0, bytes32);
+        u32x4 P[Rows], G[Rows], Mo[Rows], V[Rows];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < Rows; ++u) {
             P[u] = load16(rp, lane32 + u * kRow32);
             Mo[u] = load16(rm, lane32 + u * kRow32);
             V[u] = load16(rv, lane32 + u * kRow32);
         }
         if constexpr (kCommits<M>) {
-            const auto rg = tile_rsrc(a.g + e0, kTile * 4);
+            const auto rg = tile_rsrc(a.g + e0, bytes32);
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < Rows; ++u) {
                 G[u] = load16(rg, lane32 + u * kRow32);
             }
             if constexpr (M == Mode::CommitZeroGrad) {
                 const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
+                for (int u = 0; u < Rows; ++u) {
                     store16(zero, rg, lane32 + u * kRow32);
                 }
             }
-            const auto rb = tile_rsrc(a.b + e0, kTile * 2);
+            const auto rb = tile_rsrc(a.b + e0, bytes16);
             // Bound by HBM: each row is updated and stored as soon as it is
             // ready, with the full square root (the short in-range form of the
             // BF16-state commit measured no faster here).
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                float p[4], m[4], v[4];
+            for (int u = 0; u < Rows; ++u) {
+                    float p[4], m[4], v[4];
 #pragma unroll
                 for (int j = 0; j < kVec; ++j) {
                     p[j] = __uint_as_float(P[u][j]);
@@ -670,15 +686,16 @@ __device__ __forceinline__ uint64_t do_tile_vec(const Arrays& a, uint64_t e0, co
             }
         }
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < Rows; ++u) {
 #pragma unroll
             for (int j = 0; j < kVec; ++j) {
                 const uint32_t o = u * kBlock * kVec + j;
                 acc += ix.template hash<kTagP>(P[u][j], o) + ix.template hash<kTagM>(Mo[u][j], o) +
                        ix.template hash<kTagV>(V[u][j], o);
+                if constexpr (Masked) __builtin_amdgcn_sched_barrier(0);
             }
         }
-        return acc;
+        return Masked && threadIdx.x >= nvec ? 0 : acc;
     }
 }
 
@@ -709,32 +726,34 @@ __device__ __forceinline__ uint64_t do_scalar(const ArraysBf16& a, uint64_t e, c
     return hash_word<kTagP>(p, idx) + hash_word<kTagM>(m, idx) + hash_word<kTagV>(v, idx);
 }
 
-template <Mode M, typename Ix>
-__device__ __forceinline__ uint64_t do_tile_vec(const ArraysBf16& a, uint64_t e0, const StepScalars& sc) {
-    constexpr int kRows = kTile / (kBlock * 8);
+template <Mode M, typename Ix, int Rows, bool Masked>
+__device__ __forceinline__ uint64_t do_tile_vec(const ArraysBf16& a, uint64_t e0, uint32_t nvec,
+                                                const StepScalars& sc) {
+    static_assert(!Masked || Rows == 1, "a masked tile is one row");
     constexpr uint32_t kRowBytes = kBlock * 16;
     const uint32_t lane = threadIdx.x * 16;
+    const uint32_t bytes = Masked ? nvec * 16 : Rows * kRowBytes;
     const Ix ix(a.goff + e0, threadIdx.x * 8);  // word k of this lane: index + k
-    const auto rp = tile_rsrc(a.p + e0, kTile * 2);
-    const auto rm = tile_rsrc(a.m + e0, kTile * 2);
-    const auto rv = tile_rsrc(a.v + e0, kTile * 2);
-    u32x4 P[kRows], G[kRows], Mo[kRows], V[kRows];
+    const auto rp = tile_rsrc(a.p + e0, bytes);
+    const auto rm = tile_rsrc(a.m + e0, bytes);
+    const auto rv = tile_rsrc(a.v + e0, bytes);
+    u32x4 P[Rows], G[Rows], Mo[Rows], V[Rows];
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
+    for (int r = 0; r < Rows; ++r) {
         P[r] = load16(rp, lane + r * kRowBytes);
         Mo[r] = load16(rm, lane + r * kRowBytes);
         V[r] = load16(rv, lane + r * kRowBytes);
     }
     if constexpr (M == Mode::CommitBf16State) {
-        const auto rg = tile_rsrc(a.g + e0, kTile * 2);
+        const auto rg = tile_rsrc(a.g + e0, bytes);
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
+        for (int r = 0; r < Rows; ++r) {
             G[r] = load16(rg, lane + r * kRowBytes);
         }
-        constexpr int kN = kRows * 8;
+        constexpr int kN = Rows * 8;
         float p[kN], m[kN], v[kN];
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
+        for (int r = 0; r < Rows; ++r) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int i = r * 8 + 2 * j;
@@ -750,7 +769,7 @@ __device__ __forceinline__ uint64_t do_tile_vec(const ArraysBf16& a, uint64_t e0
         }
         adamw_steps<kN>(p, m, v, sc);
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
+        for (int r = 0; r < Rows; ++r) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int i = r * 8 + 2 * j;
@@ -765,16 +784,17 @@ __device__ __forceinline__ uint64_t do_tile_vec(const ArraysBf16& a, uint64_t e0
     }
     uint64_t acc = 0;
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
+    for (int r = 0; r < Rows; ++r) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint32_t o = r * kBlock * 8 + 2 * j;
             acc += ix.template hash<kTagP>(P[r][j] & 0xFFFFu, o) + ix.template hash<kTagP>(P[r][j] >> 16, o + 1) +
                    ix.template hash<kTagM>(Mo[r][j] & 0xFFFFu, o) + ix.template hash<kTagM>(Mo[r][j] >> 16, o + 1) +
                    ix.template hash<kTagV>(V[r][j] & 0xFFFFu, o) + ix.template hash<kTagV>(V[r][j] >> 16, o + 1);
+            if constexpr (Masked) __builtin_amdgcn_sched_barrier(0);
         }
     }
-    return acc;
+    return Masked && threadIdx.x >= nvec ? 0 : acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -784,6 +804,7 @@ __device__ __forceinline__ uint64_t do_tile_vec(const ArraysBf16& a, uint64_t e0
 // ---------------------------------------------------------------------------
 template <Mode M, typename A>
 __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t* lds) {
+    constexpr int kRows = kTile / (kBlock * kVecElems<A>);
     const uint64_t tile = blockIdx.x;
     uint32_t lo = 0, hi = bt.nseg;  // largest lo with tile_begin[lo] <= tile
     while (hi - lo > 1) {
@@ -798,7 +819,9 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
     const StepScalars sc = bt.sc[seg];
     const uint64_t seg_first = bt.elem_begin[seg];
     const uint64_t seg_end = seg_first + bt.elem_count[seg];
-    const uint64_t e0 = seg_first + (tile - bt.tile_begin[seg]) * (uint64_t)kTile;
+    const uint32_t align = bt.align[seg];
+    const uint64_t e0 = seg_first + (align == kNeverAligned ? 0 : align) +
+                        (tile - bt.tile_begin[seg]) * (uint64_t)kTile;
     // This wave's word of the workgroup sum starts at zero (LDS operations of
     // one wave are carried out in the order it issues them, so the clearing
     // comes before the wave's own additions below).
@@ -807,24 +830,50 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
         __hip_atomic_store(wave_sum, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     uint64_t acc = 0;
-    if (bt.vec_ok[seg] && e0 + kTile <= seg_end) {
-        // The short index form for tiles that do not cross a multiple of
-        // 2^32 (a uniform branch: at most one tile in 2^20 takes the other);
-        // the binary32 commits are bound by HBM, not by VALU issue, and keep
-        // the plain form (the short one measured 0.3% slower there, with one
-        // more wave per SIMD resident).
-        if (kWords16<M> && IndexLo16::applies(a.goff + e0)) {
-            acc = do_tile_vec<M, IndexLo16>(a, e0, sc);
-        } else if (!kCommits<M> && same_high_half(a.goff + e0, kTile)) {
-            acc = do_tile_vec<M, IndexHi32>(a, e0, sc);
-        } else {
-            acc = do_tile_vec<M, IndexAny>(a, e0, sc);
-        }
+    // What the tile has for the element-wise path: elements e, e + kBlock, ...
+    // below e_end.
+    uint64_t e = 0, e_end = 0;
+    if (align == kNeverAligned) {
+        e = e0 + threadIdx.x;
+        e_end = (e0 + kTile < seg_end) ? e0 + kTile : seg_end;
     } else {
-        const uint64_t e1 = (e0 + kTile < seg_end) ? e0 + kTile : seg_end;
-        for (uint64_t e = e0 + threadIdx.x; e < e1; e += kBlock) {
-            acc += do_scalar<M>(a, e, sc);
+        if (e0 + kTile <= seg_end) {
+            // The short index form for tiles that do not cross a multiple of
+            // 2^32 (a uniform branch: at most one tile in 2^20 takes the other);
+            // the binary32 commits are bound by HBM, not by VALU issue, and keep
+            // the plain form (the short one measured 0.3% slower there, with one
+            // more wave per SIMD resident).
+            if (kWords16<M> && IndexLo16::applies(a.goff + e0)) {
+                acc = do_tile_vec<M, IndexLo16, kRows, false>(a, e0, 0, sc);
+            } else if (!kCommits<M> && same_high_half(a.goff + e0, kTile)) {
+                acc = do_tile_vec<M, IndexHi32, kRows, false>(a, e0, 0, sc);
+            } else {
+                acc = do_tile_vec<M, IndexAny, kRows, false>(a, e0, 0, sc);
+            }
+        } else if (e0 < seg_end) {
+            // The last tile of a segment: whole vectors, row by row, then the
+            // elements behind them.  (With every unaligned segment and every
+            // last tile element by element a rank's 20M-element slice of an
+            // unpadded vector took 156 us per zeroing commit and 76 + 44 us per
+            // BF16 commit and digest, against 125 and 58 + 34 us.)
+            const uint32_t nvec = (uint32_t)(seg_end - e0) / kVecElems<A>;
+#pragma unroll 1
+            for (uint32_t done = 0; done < nvec; done += kBlock) {
+                acc += do_tile_vec<M, IndexAny, 1, true>(a, e0 + done * kVecElems<A>, nvec - done, sc);
+            }
+            e = e0 + nvec * kVecElems<A> + threadIdx.x;
+            e_end = seg_end;
         }
+        if (tile == bt.tile_begin[seg] && threadIdx.x >= 64) {
+            // The first tile's second wave: the elements before the first
+            // aligned one (the segment may end among them).
+            e = seg_first + threadIdx.x - 64;
+            e_end = seg_first + align < seg_end ? seg_first + align : seg_end;
+        }
+    }
+#pragma unroll 1
+    for (; e < e_end; e += kBlock) {
+        acc += do_scalar<M>(a, e, sc);
     }
     // Workgroup sum: every lane adds its share into its wave's LDS word with
     // one 64-bit LDS atomic (no VALU work: a shuffle tree costs about fifty

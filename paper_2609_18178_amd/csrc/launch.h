@@ -44,9 +44,14 @@ struct StepScalars {
     float beta1, beta2, eps, decay, omb1, omb2, step_size, rs_bc2;
 };
 
+// A segment whose arrays are nowhere 16-byte (fp32 and BF16 state) and 8-byte
+// (bf16 copy) aligned at the same element.
+constexpr uint32_t kNeverAligned = ~0u;
+
 // One launch's slice of the segment table.  Tiles never straddle segments:
 // segment s owns tiles [tile_begin[s], tile_begin[s+1]), at
-// least one (an empty segment's tile hands in a share of zero).
+// least one (an empty segment's tile hands in a share of zero); they cover its
+// elements from the first aligned one on, and the first tile those before it.
 struct Batch {
     uint32_t nseg;
     uint32_t slot0;        // result slot of this batch's first segment
@@ -55,7 +60,7 @@ struct Batch {
     uint64_t tile_begin[kSegsPerLaunch + 1];
     uint64_t elem_begin[kSegsPerLaunch];  // shard-relative first element
     uint64_t elem_count[kSegsPerLaunch];
-    uint32_t vec_ok[kSegsPerLaunch];      // 16-B (fp32) / 8-B (bf16) aligned start
+    uint32_t align[kSegsPerLaunch];       // elements before the first aligned one, or kNeverAligned
     StepScalars sc[kSegsPerLaunch];
 };
 

@@ -317,7 +317,7 @@ int check_segment_hypers(const View& s) {
 
 bool is_bf16_state(pact::Mode m) { return m == pact::Mode::CommitBf16State || m == pact::Mode::DigestBf16State; }
 
-// Whether a segment starting at element `first` can take the vector path:
+// Whether the vector path can start at element `first`:
 // 16-byte aligned in every array the mode moves as 16-byte vectors, 8-byte in
 // the bf16 working copy.
 bool vector_ok(pact::Mode mode, const View& s, uint64_t first) {
@@ -341,9 +341,22 @@ bool vector_ok(pact::Mode mode, const View& s, uint64_t first) {
     return false;
 }
 
+// Elements of a segment before the first one from which the vector path can
+// start, or kNeverAligned.
+uint32_t align_of(pact::Mode mode, const View& s, uint64_t first) {
+    const uint32_t vec = is_bf16_state(mode) ? 8 : pact::kVec;
+    for (uint32_t h = 0; h < vec; ++h) {
+        if (vector_ok(mode, s, first + h)) return h;
+    }
+    return pact::kNeverAligned;
+}
+
 // Tiles of a segment.  An empty one (an empty shard too) has one: it is the
 // tiles that write the result slots.
-uint64_t tiles_of(uint64_t count) { return std::max<uint64_t>(1, (count + pact::kTile - 1) / pact::kTile); }
+uint64_t tiles_of(uint64_t count, uint32_t align) {
+    const uint64_t head = align == pact::kNeverAligned ? 0 : std::min<uint64_t>(align, count);
+    return std::max<uint64_t>(1, (count - head + pact::kTile - 1) / pact::kTile);
+}
 
 // What the caller says about the workspace: clean = every node is zero (the
 // tile kernels leave them so), and the clearing launch is skipped; odd = the
@@ -366,7 +379,9 @@ int run(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, ui
     const size_t nwork = work.count();
     if (per_segment && res.words != nullptr) {
         uint64_t all = 0;
-        for (size_t k = 0; k < nwork; ++k) all += tiles_of(s.segs[k].length);
+        for (size_t k = 0; k < nwork; ++k) {
+            all += tiles_of(s.segs[k].length, align_of(mode, s, s.segs[k].offset));
+        }
         if (all <= pact::kGatherTiles) res.total_tiles = (uint32_t)all;
     }
     hipError_t e = hipSuccess;
@@ -408,14 +423,15 @@ int run(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, ui
         size_t cnt = 0;
         for (; cnt < (size_t)pact::kSegsPerLaunch && first + cnt < nwork; ++cnt) {
             const SegWork w = work.at(first + cnt);
-            const uint64_t t = tiles_of(w.count);
+            const uint32_t align = align_of(mode, s, w.first);
+            const uint64_t t = tiles_of(w.count, align);
             if (tiles + t > kMaxTiles) break;
             b.tile_begin[cnt] = tiles;
             tiles += t;
             b.elem_begin[cnt] = w.first;
             b.elem_count[cnt] = w.count;
             b.sc[cnt] = w.sc;
-            b.vec_ok[cnt] = vector_ok(mode, s, w.first) ? 1u : 0u;
+            b.align[cnt] = align;
         }
         b.nseg = (uint32_t)cnt;
         b.tile_begin[cnt] = tiles;
