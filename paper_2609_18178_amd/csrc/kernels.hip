@@ -94,6 +94,12 @@ __device__ __forceinline__ uint64_t hash_word(uint32_t word, uint64_t index) {
     return splitmix_mix(((uint64_t)word ^ index) + kAdd);
 }
 
+// A wave-uniform value, in scalar registers.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ uint64_t uniform(uint64_t x) {
+    return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
+}
+
 // The indices of the digest words of one vector tile, as seen by one lane:
 // word `off` of the lane sits at flat index first + off.
 //
@@ -232,10 +238,10 @@ struct IndexLo16 {
     uint32_t lo;       // low half of the lane's first index
     uint32_t u[4];     // U_k per tag
     uint64_t khi[4];   // K_k << 32 per tag
-    // Whether the tile of kTile indices from `first` on may take this form
+    // Whether the tile of n indices from `first` on may take this form
     // (wave-uniform).
-    static __device__ __forceinline__ bool applies(uint64_t first) {
-        if ((first >> 16) != ((first + kTile - 1) >> 16)) {
+    static __device__ __forceinline__ bool applies(uint64_t first, uint32_t n) {
+        if ((first >> 16) != ((first + n - 1) >> 16)) {
             return false;
         }
         const uint32_t b_lo = ((uint32_t)first & 0xFFFF0000u) + kGammaLo;
@@ -268,12 +274,6 @@ struct IndexLo16 {
         return mix_after_first_round(prod, lo1 * chi);
     }
 };
-
-// Elements of one vector of a tile.
-template <typename A>
-constexpr uint32_t kVecElems = kVec;
-template <>
-constexpr uint32_t kVecElems<ArraysBf16> = 8;
 
 // Whether the `count` indices from `first` on share their upper 32 bits.
 __device__ __forceinline__ bool same_high_half(uint64_t first, uint64_t count) {
@@ -461,44 +461,52 @@ __device__ __forceinline__ void node_clear(uint64_t* word) {
 }
 
 // One tile hands in its share s to the result at dst, as number `index` of the
-// result's n tiles: one thread for word 0 and one for word 1, in the same
-// instructions.  Lane l's node is at lanes + l * kLaneStride.  (A wait for an
-// atomic's result waits for the stores before it too, so every store is issued
-// behind the next atomic.)
+// result's n tiles: lanes 0 and 1 of one wave, for word 0 and word 1, in the same
+// instructions (everything but s and the words themselves is wave-uniform: the
+// 60 VALU instructions that this took at first were 1% of a state digest).
+// Lane l's node is at lanes + l * kLaneStride.  (A wait for an atomic's result
+// waits for the stores before it too, so every store is issued behind the next
+// atomic.)
 __device__ __forceinline__ void hand_in(uint64_t* lanes, uint64_t* own, uint64_t* dst, uint32_t n, uint32_t index,
-                                        bool low, uint64_t s) {
+                                        uint64_t s) {
+    const uint32_t word = threadIdx.x & 1;
+    const bool low = word == 0;
     const bool spread = n > kSpreadTiles;
     const uint32_t l = index & (kLanes - 1);
-    const uint32_t word = low ? 0u : 1u;
-    uint64_t* const first = (spread ? lanes + l * kLaneStride : own) + word;
+    uint64_t* const first = spread ? lanes + l * kLaneStride : own;
     const uint32_t in_first = spread ? (n - l + kLanes - 1) / kLanes : n;  // the tiles that arrive there
     const uint32_t in_own = spread ? (uint32_t)kLanes : n;
-    uint64_t part = low ? s & kLowMask : s & ~kLowMask;
-    uint64_t old = node_add(first, part + (low ? 1ull << kCountAtTiles : 1ull));
-    // word 1 of the own node gets word 0's carry besides
-    if ((low ? (uint32_t)(old >> kCountAtTiles) + 1u
-             : (uint32_t)(old & kLowMask) + (spread ? 1u : 0u)) != in_first) {
-        return;
-    }
-    part += low ? old & ((1ull << kCountAtTiles) - 1) : old & ~kLowMask;
+    // this word's part of a sum, and one arrival
+    auto part_of = [&](uint64_t x, int count_at) {
+        const uint64_t low_part = x & ((1ull << count_at) - 1), high_part = x & ~kLowMask;
+        return low ? low_part : high_part;
+    };
+    auto arrivals = [&](uint64_t x, int count_at) {
+        const uint32_t at_low = (uint32_t)(x >> count_at), at_high = (uint32_t)x & (uint32_t)kLowMask;
+        return low ? at_low : at_high;
+    };
+    uint64_t part = part_of(s, kLowBits);
+    uint64_t old = node_add(first + word, part + (low ? 1ull << kCountAtTiles : 1ull));
+    // (word 1 of the own node gets word 0's carry besides)
+    if (arrivals(old, kCountAtTiles) != (low || spread ? in_first - 1 : in_first)) return;
+    part += part_of(old, kCountAtTiles);
     if (spread) {
         old = node_add(own + word, part + (low ? 1ull << kCountAtLanes : 1ull));
-        node_clear(first);
-        if ((low ? (uint32_t)(old >> kCountAtLanes) + 1u : (uint32_t)(old & kLowMask)) != in_own) return;
-        part += low ? old & ((1ull << kCountAtLanes) - 1) : old & ~kLowMask;
+        node_clear(first + word);
+        if (arrivals(old, kCountAtLanes) != (low ? in_own - 1 : in_own)) return;
+        part += part_of(old, kCountAtLanes);
     }
+    uint8_t* const b = reinterpret_cast<uint8_t*>(dst);
     if (low) {
         const uint64_t carry = part & ~kLowMask;
         old = node_add(own + 1, carry + 1u);
         node_clear(own);
-        uint8_t* const b = reinterpret_cast<uint8_t*>(dst);
         *reinterpret_cast<uint16_t*>(b) = (uint16_t)part;
         b[2] = (uint8_t)(part >> 16);
         if ((uint32_t)(old & kLowMask) != in_own) return;
         part = (old & ~kLowMask) + carry;
     }
     node_clear(own + 1);
-    uint8_t* const b = reinterpret_cast<uint8_t*>(dst);
     b[3] = (uint8_t)(part >> kLowBits);
     *reinterpret_cast<uint32_t*>(b + 4) = (uint32_t)(part >> 32);
 }
@@ -550,11 +558,31 @@ __device__ __forceinline__ void store8(u32x2 x, __amdgpu_buffer_rsrc_t r, uint32
     __builtin_amdgcn_raw_buffer_store_b64(x, r, (int)off, 0, kNonTemporal);
 }
 
+// A vector of eight or four 16-bit words.
+template <int Vec>
+struct Words16;
+template <>
+struct Words16<8> {
+    typedef u32x4 type;
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t off) { return load16(r, off); }
+    static __device__ __forceinline__ void store(type x, __amdgpu_buffer_rsrc_t r, uint32_t off) { store16(x, r, off); }
+};
+template <>
+struct Words16<4> {
+    typedef u32x2 type;
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t off) { return load8(r, off); }
+    static __device__ __forceinline__ void store(type x, __amdgpu_buffer_rsrc_t r, uint32_t off) { store8(x, r, off); }
+};
+
 // ---------------------------------------------------------------------------
 // one element, element-wise path (ragged tails, misaligned segments)
 // ---------------------------------------------------------------------------
 template <Mode M>
 constexpr bool kCommits = (M == Mode::Commit || M == Mode::CommitZeroGrad);
+
+// Modes whose tiles may have several passes.
+template <Mode M>
+constexpr bool kManyPasses = (M == Mode::Bf16Digest || M == Mode::DigestBf16State);
 
 // Modes whose digest words have 16 bits (the short IndexLo16 form applies).
 template <Mode M>
@@ -587,24 +615,26 @@ __device__ __forceinline__ uint64_t do_scalar(const Arrays& a, uint64_t e, const
 }
 
 // ---------------------------------------------------------------------------
-// one tile whose start is 16-byte aligned in every fp32 array (8-byte in the
-// bf16 array): Rows rows of kBlock 16-byte vectors per array.  Row u, lane t
-// holds elements e0 + u*kBlock*4 + 4t .. +3.  Masked: one row of which only the
+// one pass of a tile, whose start is 16-byte aligned in every fp32 array (8-byte in the
+// bf16 array): Rows rows of kBlock vectors per array.  Row u, lane t holds
+// elements e0 + (u*kBlock + t)*Vec .. + Vec - 1 (Vec is 4 in the modes that read
+// fp32 arrays, 16-byte vectors).  Masked: one row of which only the
 // first nvec vectors exist; the buffer range check drops the others' loads and
 // stores (whole vectors, since the range ends with one), and their hashes are
 // not counted (and go one element after another: it is not to cost the full
 // tiles registers).
 // ---------------------------------------------------------------------------
-template <Mode M, typename Ix, int Rows, bool Masked>
+template <Mode M, typename Ix, int Vec, int Rows, bool Masked>
 __device__ __forceinline__ uint64_t do_tile_vec(const Arrays& a, uint64_t e0, uint32_t nvec, const StepScalars& sc) {
-    constexpr uint32_t kRow32 = kBlock * kVec * 4;  // bytes of one fp32 row
-    constexpr uint32_t kRow16 = kBlock * kVec * 2;  // bytes of one bf16 row
+    static_assert(Vec == 4 || M == Mode::Bf16Digest, "16-byte vectors of fp32");
+    constexpr uint32_t kRow32 = kBlock * Vec * 4;  // bytes of one fp32 row
+    constexpr uint32_t kRow16 = kBlock * Vec * 2;  // bytes of one bf16 row
     static_assert(!Masked || Rows == 1, "a masked tile is one row");
-    const uint32_t bytes32 = Masked ? nvec * kVec * 4 : Rows * kRow32;
-    const uint32_t bytes16 = Masked ? nvec * kVec * 2 : Rows * kRow16;
-    const uint32_t lane32 = threadIdx.x * kVec * 4;
-    const uint32_t lane16 = threadIdx.x * kVec * 2;
-    const Ix ix(a.goff + e0, threadIdx.x * kVec);  // word k of this lane: index + k
+    const uint32_t bytes32 = Masked ? nvec * Vec * 4 : Rows * kRow32;
+    const uint32_t bytes16 = Masked ? nvec * Vec * 2 : Rows * kRow16;
+    const uint32_t lane32 = threadIdx.x * Vec * 4;
+    const uint32_t lane16 = threadIdx.x * Vec * 2;
+    const Ix ix(a.goff + e0, threadIdx.x * Vec);  // word k of this lane: index + k
     uint64_t acc = 0;
     if constexpr (M == Mode::GradGuard) {
         const auto rg = tile_rsrc(a.g + e0, bytes32);
@@ -616,23 +646,26 @@ __device__ __forceinline__ uint64_t do_tile_vec(const Arrays& a, uint64_t e0, ui
 #pragma unroll
         for (int u = 0; u < Rows; ++u) {
 #pragma unroll
-            for (int j = 0; j < kVec; ++j) {
+            for (int j = 0; j < Vec; ++j) {
                 acc += G[u][j] != 0u ? 1u : 0u;  // a dropped load reads zero
             }
         }
         return acc;
     } else if constexpr (M == Mode::Bf16Digest) {
         const auto rb = tile_rsrc(a.b + e0, bytes16);
-        u32x2 W[Rows];
+        typename Words16<Vec>::type W[Rows];
 #pragma unroll
         for (int u = 0; u < Rows; ++u) {
-            W[u] = load8(rb, lane16 + u * kRow16);
+            W[u] = Words16<Vec>::load(rb, lane16 + u * kRow16);
         }
 #pragma unroll
         for (int u = 0; u < Rows; ++u) {
-            const uint32_t o = u * kBlock * kVec;
-            acc += ix.template hash<kTagB>(W[u].x & 0xFFFFu, o) + ix.template hash<kTagB>(W[u].x >> 16, o + 1) +
-                   ix.template hash<kTagB>(W[u].y & 0xFFFFu, o + 2) + ix.template hash<kTagB>(W[u].y >> 16, o + 3);
+#pragma unroll
+            for (int j = 0; j < Vec / 2; ++j) {
+                const uint32_t o = u * kBlock * Vec + 2 * j;
+                acc += ix.template hash<kTagB>(W[u][j] & 0xFFFFu, o) + ix.template hash<kTagB>(W[u][j] >> 16, o + 1);
+                if constexpr (Masked) __builtin_amdgcn_sched_barrier(0);
+            }
         }
         return Masked && threadIdx.x >= nvec ? 0 : acc;
     } else {
@@ -667,7 +700,7 @@ __device__ __forceinline__ uint64_t do_tile_vec(const Arrays& a, uint64_t e0, ui
             for (int u = 0; u < Rows; ++u) {
                     float p[4], m[4], v[4];
 #pragma unroll
-                for (int j = 0; j < kVec; ++j) {
+                for (int j = 0; j < Vec; ++j) {
                     p[j] = __uint_as_float(P[u][j]);
                     m[j] = __uint_as_float(Mo[u][j]);
                     v[j] = __uint_as_float(V[u][j]);
@@ -688,8 +721,8 @@ __device__ __forceinline__ uint64_t do_tile_vec(const Arrays& a, uint64_t e0, ui
 #pragma unroll
         for (int u = 0; u < Rows; ++u) {
 #pragma unroll
-            for (int j = 0; j < kVec; ++j) {
-                const uint32_t o = u * kBlock * kVec + j;
+            for (int j = 0; j < Vec; ++j) {
+                const uint32_t o = u * kBlock * Vec + j;
                 acc += ix.template hash<kTagP>(P[u][j], o) + ix.template hash<kTagM>(Mo[u][j], o) +
                        ix.template hash<kTagV>(V[u][j], o);
                 if constexpr (Masked) __builtin_amdgcn_sched_barrier(0);
@@ -700,9 +733,8 @@ __device__ __forceinline__ uint64_t do_tile_vec(const Arrays& a, uint64_t e0, ui
 }
 
 // ---------------------------------------------------------------------------
-// BF16 state: a tile is kTile / (kBlock * 8) rows of kBlock 16-byte vectors
-// (eight bf16 words each) per array; element 2j of a vector is the low half
-// of its word j.
+// BF16 state: vectors of Vec (eight or four) bf16 words per array; element 2j
+// of a vector is the low half of its word j.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float widen_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float widen_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
@@ -726,37 +758,38 @@ __device__ __forceinline__ uint64_t do_scalar(const ArraysBf16& a, uint64_t e, c
     return hash_word<kTagP>(p, idx) + hash_word<kTagM>(m, idx) + hash_word<kTagV>(v, idx);
 }
 
-template <Mode M, typename Ix, int Rows, bool Masked>
+template <Mode M, typename Ix, int Vec, int Rows, bool Masked>
 __device__ __forceinline__ uint64_t do_tile_vec(const ArraysBf16& a, uint64_t e0, uint32_t nvec,
                                                 const StepScalars& sc) {
     static_assert(!Masked || Rows == 1, "a masked tile is one row");
-    constexpr uint32_t kRowBytes = kBlock * 16;
-    const uint32_t lane = threadIdx.x * 16;
-    const uint32_t bytes = Masked ? nvec * 16 : Rows * kRowBytes;
-    const Ix ix(a.goff + e0, threadIdx.x * 8);  // word k of this lane: index + k
+    using W = Words16<Vec>;
+    constexpr uint32_t kRowBytes = kBlock * Vec * 2;
+    const uint32_t lane = threadIdx.x * Vec * 2;
+    const uint32_t bytes = Masked ? nvec * Vec * 2 : Rows * kRowBytes;
+    const Ix ix(a.goff + e0, threadIdx.x * Vec);  // word k of this lane: index + k
     const auto rp = tile_rsrc(a.p + e0, bytes);
     const auto rm = tile_rsrc(a.m + e0, bytes);
     const auto rv = tile_rsrc(a.v + e0, bytes);
-    u32x4 P[Rows], G[Rows], Mo[Rows], V[Rows];
+    typename W::type P[Rows], G[Rows], Mo[Rows], V[Rows];
 #pragma unroll
     for (int r = 0; r < Rows; ++r) {
-        P[r] = load16(rp, lane + r * kRowBytes);
-        Mo[r] = load16(rm, lane + r * kRowBytes);
-        V[r] = load16(rv, lane + r * kRowBytes);
+        P[r] = W::load(rp, lane + r * kRowBytes);
+        Mo[r] = W::load(rm, lane + r * kRowBytes);
+        V[r] = W::load(rv, lane + r * kRowBytes);
     }
     if constexpr (M == Mode::CommitBf16State) {
         const auto rg = tile_rsrc(a.g + e0, bytes);
 #pragma unroll
         for (int r = 0; r < Rows; ++r) {
-            G[r] = load16(rg, lane + r * kRowBytes);
+            G[r] = W::load(rg, lane + r * kRowBytes);
         }
-        constexpr int kN = Rows * 8;
+        constexpr int kN = Rows * Vec;
         float p[kN], m[kN], v[kN];
 #pragma unroll
         for (int r = 0; r < Rows; ++r) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = r * 8 + 2 * j;
+            for (int j = 0; j < Vec / 2; ++j) {
+                const int i = r * Vec + 2 * j;
                 p[i] = widen_lo(P[r][j]);
                 p[i + 1] = widen_hi(P[r][j]);
                 m[i] = widen_lo(Mo[r][j]);
@@ -771,23 +804,23 @@ __device__ __forceinline__ uint64_t do_tile_vec(const ArraysBf16& a, uint64_t e0
 #pragma unroll
         for (int r = 0; r < Rows; ++r) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = r * 8 + 2 * j;
+            for (int j = 0; j < Vec / 2; ++j) {
+                const int i = r * Vec + 2 * j;
                 P[r][j] = to_bf16x2(p[i], p[i + 1]);
                 Mo[r][j] = to_bf16x2(m[i], m[i + 1]);
                 V[r][j] = to_bf16x2(v[i], v[i + 1]);
             }
-            store16(P[r], rp, lane + r * kRowBytes);
-            store16(Mo[r], rm, lane + r * kRowBytes);
-            store16(V[r], rv, lane + r * kRowBytes);
+            W::store(P[r], rp, lane + r * kRowBytes);
+            W::store(Mo[r], rm, lane + r * kRowBytes);
+            W::store(V[r], rv, lane + r * kRowBytes);
         }
     }
     uint64_t acc = 0;
 #pragma unroll
     for (int r = 0; r < Rows; ++r) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t o = r * kBlock * 8 + 2 * j;
+        for (int j = 0; j < Vec / 2; ++j) {
+            const uint32_t o = r * kBlock * Vec + 2 * j;
             acc += ix.template hash<kTagP>(P[r][j] & 0xFFFFu, o) + ix.template hash<kTagP>(P[r][j] >> 16, o + 1) +
                    ix.template hash<kTagM>(Mo[r][j] & 0xFFFFu, o) + ix.template hash<kTagM>(Mo[r][j] >> 16, o + 1) +
                    ix.template hash<kTagV>(V[r][j] & 0xFFFFu, o) + ix.template hash<kTagV>(V[r][j] >> 16, o + 1);
@@ -802,10 +835,30 @@ __device__ __forceinline__ uint64_t do_tile_vec(const ArraysBf16& a, uint64_t e0
 // the batch's tile prefix (kernel arguments, scalar loads); the tile's digest
 // share is summed over the workgroup in LDS and added with one 64-bit atomic.
 // ---------------------------------------------------------------------------
-template <Mode M, typename A>
+// The tile of this block, with runs of `run` tiles per XCD; the blocks behind
+// the last whole group keep their order.
+__device__ __forceinline__ uint32_t dealt_tile(uint32_t run) {
+    const uint32_t group = kXcds * run;
+    const uint32_t r = blockIdx.x % group, first = blockIdx.x - r;
+    return gridDim.x - first >= group ? first + r % kXcds * run + r / kXcds : blockIdx.x;
+}
+
+template <Mode M, bool Small>
+__device__ __forceinline__ uint32_t tile_of_block() {
+    constexpr Runs kRuns = runs_of(M, Small);
+    if (gridDim.x >= kRuns.long_from) return dealt_tile(kRuns.long_run);
+    if (gridDim.x >= kRuns.from) return dealt_tile(kRuns.run);
+    return blockIdx.x;
+}
+
+template <Mode M, bool Small, typename A>
 __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t* lds) {
-    constexpr int kRows = kTile / (kBlock * kVecElems<A>);
-    const uint64_t tile = blockIdx.x;
+    constexpr Shape kShape = shape_of(M, Small);
+    constexpr int kVecs = kShape.vec, kRows = kShape.rows;
+    constexpr uint32_t kPass = kShape.elems();
+    const uint32_t passes = kManyPasses<M> && !Small ? bt.passes : 1;
+    const uint32_t tile_elems = kPass * passes;
+    const uint64_t tile = tile_of_block<M, Small>();
     uint32_t lo = 0, hi = bt.nseg;  // largest lo with tile_begin[lo] <= tile
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
@@ -821,7 +874,7 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
     const uint64_t seg_end = seg_first + bt.elem_count[seg];
     const uint32_t align = bt.align[seg];
     const uint64_t e0 = seg_first + (align == kNeverAligned ? 0 : align) +
-                        (tile - bt.tile_begin[seg]) * (uint64_t)kTile;
+                        (tile - bt.tile_begin[seg]) * (uint64_t)tile_elems;
     // This wave's word of the workgroup sum starts at zero (LDS operations of
     // one wave are carried out in the order it issues them, so the clearing
     // comes before the wave's own additions below).
@@ -835,33 +888,43 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
     uint64_t e = 0, e_end = 0;
     if (align == kNeverAligned) {
         e = e0 + threadIdx.x;
-        e_end = (e0 + kTile < seg_end) ? e0 + kTile : seg_end;
+        e_end = (e0 + tile_elems < seg_end) ? e0 + tile_elems : seg_end;
     } else {
-        if (e0 + kTile <= seg_end) {
-            // The short index form for tiles that do not cross a multiple of
-            // 2^32 (a uniform branch: at most one tile in 2^20 takes the other);
+        const uint64_t left = e0 < seg_end ? seg_end - e0 : 0;
+        const uint32_t whole = left < tile_elems ? (uint32_t)left / kPass : passes;  // the tile's whole passes
+        auto one_pass = [&](uint64_t at) {
+            // The short index form for passes that do not cross a multiple of
+            // 2^32 (a uniform branch: at most one in 2^20 takes the other);
             // the binary32 commits are bound by HBM, not by VALU issue, and keep
             // the plain form (the short one measured 0.3% slower there, with one
             // more wave per SIMD resident).
-            if (kWords16<M> && IndexLo16::applies(a.goff + e0)) {
-                acc = do_tile_vec<M, IndexLo16, kRows, false>(a, e0, 0, sc);
-            } else if (!kCommits<M> && same_high_half(a.goff + e0, kTile)) {
-                acc = do_tile_vec<M, IndexHi32, kRows, false>(a, e0, 0, sc);
+            if (kWords16<M> && IndexLo16::applies(a.goff + at, kPass)) {
+                acc += do_tile_vec<M, IndexLo16, kVecs, kRows, false>(a, at, 0, sc);
+            } else if (!kCommits<M> && same_high_half(a.goff + at, kPass)) {
+                acc += do_tile_vec<M, IndexHi32, kVecs, kRows, false>(a, at, 0, sc);
             } else {
-                acc = do_tile_vec<M, IndexAny, kRows, false>(a, e0, 0, sc);
+                acc += do_tile_vec<M, IndexAny, kVecs, kRows, false>(a, at, 0, sc);
             }
-        } else if (e0 < seg_end) {
-            // The last tile of a segment: whole vectors, row by row, then the
+        };
+        if constexpr (kManyPasses<M> && !Small) {
+#pragma unroll 1
+            for (uint32_t pass = 0; pass < whole; ++pass) one_pass(uniform(e0 + pass * kPass));
+        } else if (whole != 0) {
+            one_pass(e0);
+        }
+        const uint64_t at = e0 + whole * kPass;
+        if (whole < passes && at < seg_end) {
+            // The last pass of a segment: whole vectors, row by row, then the
             // elements behind them.  (With every unaligned segment and every
             // last tile element by element a rank's 20M-element slice of an
             // unpadded vector took 156 us per zeroing commit and 76 + 44 us per
             // BF16 commit and digest, against 125 and 58 + 34 us.)
-            const uint32_t nvec = (uint32_t)(seg_end - e0) / kVecElems<A>;
+            const uint32_t nvec = (uint32_t)(seg_end - at) / kVecs;
 #pragma unroll 1
             for (uint32_t done = 0; done < nvec; done += kBlock) {
-                acc += do_tile_vec<M, IndexAny, 1, true>(a, e0 + done * kVecElems<A>, nvec - done, sc);
+                acc += do_tile_vec<M, IndexAny, kVecs, 1, true>(a, at + done * kVecs, nvec - done, sc);
             }
-            e = e0 + nvec * kVecElems<A> + threadIdx.x;
+            e = at + nvec * kVecs + threadIdx.x;
             e_end = seg_end;
         }
         if (tile == bt.tile_begin[seg] && threadIdx.x >= 64) {
@@ -882,8 +945,11 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
     __hip_atomic_fetch_add(wave_sum, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __syncthreads();
     const uint32_t slot = bt.per_segment ? bt.slot0 + seg : 0;
-    const uint32_t in_seg = (uint32_t)(tile - bt.tile_begin[seg]);
-    if (threadIdx.x < 4) {
+    const uint32_t in_seg = uniform((uint32_t)(tile - bt.tile_begin[seg]));
+    // wave 0 for the slot, wave 1 for the total, whose nodes sit beside slot 0's
+    const uint32_t wave = uniform(threadIdx.x >> 6);
+    const bool total = wave == 1;
+    if (wave == 0 || (total && a.res.total_tiles != 0)) {
         uint64_t s = 0;
 #pragma unroll
         for (int w = 0; w < kBlock / 64; ++w) {
@@ -893,16 +959,13 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
             if (threadIdx.x == 0 && s != 0) {
                 atomicAdd(reinterpret_cast<unsigned long long*>(a.res.digest + slot), (unsigned long long)s);
             }
-        } else if (threadIdx.x < 2 || a.res.total_tiles != 0) {
-            // threads 0 and 1 for the slot, 2 and 3 for the total, whose nodes
-            // sit beside slot 0's
-            const bool total = threadIdx.x >= 2;
-            const uint32_t n = (uint32_t)(bt.tile_begin[seg + 1] - bt.tile_begin[seg]);
+        } else if ((threadIdx.x & 63) < 2) {
+            const uint32_t n = uniform((uint32_t)(bt.tile_begin[seg + 1] - bt.tile_begin[seg]));
             uint64_t* const line0 = a.res.words + a.res.set * 2;
             uint64_t* const line = line0 + (uint64_t)slot * kLanes * kLaneStride;
             hand_in(total ? line0 + 8 : line, total ? line0 + kLaneStride + 4 : line + 4,
                     a.res.digest + (total ? a.res.total_slot : slot), total ? a.res.total_tiles : n,
-                    total ? bt.tile0 + (uint32_t)tile : in_seg, (threadIdx.x & 1) == 0, s);
+                    total ? bt.tile0 + uniform((uint32_t)tile) : in_seg, s);
         }
     }
     if (a.res.words != nullptr && in_seg == 0) {
@@ -918,21 +981,21 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
 // five; it takes 79 VGPRs, six waves (capped at seven it spills).
 template <Mode M>
 constexpr unsigned kMinWavesPerSimd = (M == Mode::StateDigest || M == Mode::DigestBf16State) ? 8u
-                                      : (M == Mode::CommitBf16State)                         ? 5u
+                                      : (M == Mode::CommitBf16State)                         ? 6u
                                                                                              : 1u;
 
-template <Mode M>
+template <Mode M, bool Small>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWavesPerSimd<M>)))
 void tile_kernel(Arrays a, Batch bt) {
     __shared__ uint64_t lds[kBlock / 64];
-    tile_body<M>(a, bt, lds);
+    tile_body<M, Small>(a, bt, lds);
 }
 
-template <Mode M>
+template <Mode M, bool Small>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWavesPerSimd<M>)))
 void tile_kernel_bf16(ArraysBf16 a, Batch bt) {
     __shared__ uint64_t lds[kBlock / 64];
-    tile_body<M>(a, bt, lds);
+    tile_body<M, Small>(a, bt, lds);
 }
 
 // Clears what the tile kernels hand their shares in to: every node of both
@@ -1041,39 +1104,70 @@ hipError_t launch_clear(uint64_t* digest, uint64_t* words, uint32_t nres, uint32
     return hipGetLastError();
 }
 
-hipError_t launch_batch(Mode mode, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream) {
+namespace {
+
+// LDS reserved per workgroup beyond what it uses: holds the binary32 commits
+// at five workgroups per CU.
+//
+// A commit reads four arrays and writes four, and HBM gives such a mix its
+// reading rate only while few rows are open: what counts is how much of each
+// array is in flight at a time, and in what order.  Tiles of 16 KB per array, as
+// many as fit (four per CU), kept 16 MB of each in flight; tiles of 4 KB, five per
+// CU, keep 5 MB, and runs of neighbouring tiles per XCD keep that in a few
+// stretches.  One commit of 453,001,472 elements, the arrays in five separate
+// allocations, us (TB/s), and in an arena (arrays 44 GiB apart):
+//   16 KB tiles, four per CU               2420 (5.62)   2095
+//   4 KB tiles, eight per CU               2360 (5.76)   2101
+//   4 KB tiles, five per CU                2272 (5.98)   2105
+//   4 KB tiles, eight per CU, runs of 32   2251 (6.04)   2092
+//   4 KB tiles, five per CU, runs of 32    2205 (6.16)   2078
+//   4 KB tiles, four per CU, runs of 32    2170 (6.26)   2117
+//   4 KB tiles, three per CU               2721 (4.99)
+// Five rather than four keeps the arena's rate.  The 16-bit state's commit and
+// the digests were slower with less in flight.
+template <Mode M>
+constexpr uint32_t kReserveLds = kCommits<M> ? 30u << 10 : 0u;
+
+template <Mode M>
+void launch_tiles(bool small, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream) {
+    if constexpr (small_up_to(M) != 0) {
+        if (small) {
+            hipLaunchKernelGGL((tile_kernel<M, true>), dim3(grid), dim3(kBlock), 0, stream, a, b);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((tile_kernel<M, false>), dim3(grid), dim3(kBlock), kReserveLds<M>, stream, a, b);
+}
+
+template <Mode M>
+void launch_tiles(bool small, const ArraysBf16& a, const Batch& b, uint32_t grid, hipStream_t stream) {
+    if (small) {
+        hipLaunchKernelGGL((tile_kernel_bf16<M, true>), dim3(grid), dim3(kBlock), 0, stream, a, b);
+    } else {
+        hipLaunchKernelGGL((tile_kernel_bf16<M, false>), dim3(grid), dim3(kBlock), 0, stream, a, b);
+    }
+}
+
+}  // namespace
+
+hipError_t launch_batch(Mode mode, bool small, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream) {
     switch (mode) {
-        case Mode::Commit:
-            hipLaunchKernelGGL(tile_kernel<Mode::Commit>, dim3(grid), dim3(kBlock), 0, stream, a, b);
-            break;
-        case Mode::StateDigest:
-            hipLaunchKernelGGL(tile_kernel<Mode::StateDigest>, dim3(grid), dim3(kBlock), 0, stream, a, b);
-            break;
-        case Mode::Bf16Digest:
-            hipLaunchKernelGGL(tile_kernel<Mode::Bf16Digest>, dim3(grid), dim3(kBlock), 0, stream, a, b);
-            break;
-        case Mode::CommitZeroGrad:
-            hipLaunchKernelGGL(tile_kernel<Mode::CommitZeroGrad>, dim3(grid), dim3(kBlock), 0, stream, a, b);
-            break;
-        case Mode::GradGuard:
-            hipLaunchKernelGGL(tile_kernel<Mode::GradGuard>, dim3(grid), dim3(kBlock), 0, stream, a, b);
-            break;
-        default:
-            return hipErrorInvalidValue;
+        case Mode::Commit: launch_tiles<Mode::Commit>(small, a, b, grid, stream); break;
+        case Mode::StateDigest: launch_tiles<Mode::StateDigest>(small, a, b, grid, stream); break;
+        case Mode::Bf16Digest: launch_tiles<Mode::Bf16Digest>(small, a, b, grid, stream); break;
+        case Mode::CommitZeroGrad: launch_tiles<Mode::CommitZeroGrad>(small, a, b, grid, stream); break;
+        case Mode::GradGuard: launch_tiles<Mode::GradGuard>(small, a, b, grid, stream); break;
+        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_batch_bf16(Mode mode, const ArraysBf16& a, const Batch& b, uint32_t grid, hipStream_t stream) {
+hipError_t launch_batch_bf16(Mode mode, bool small, const ArraysBf16& a, const Batch& b, uint32_t grid,
+                             hipStream_t stream) {
     switch (mode) {
-        case Mode::CommitBf16State:
-            hipLaunchKernelGGL(tile_kernel_bf16<Mode::CommitBf16State>, dim3(grid), dim3(kBlock), 0, stream, a, b);
-            break;
-        case Mode::DigestBf16State:
-            hipLaunchKernelGGL(tile_kernel_bf16<Mode::DigestBf16State>, dim3(grid), dim3(kBlock), 0, stream, a, b);
-            break;
-        default:
-            return hipErrorInvalidValue;
+        case Mode::CommitBf16State: launch_tiles<Mode::CommitBf16State>(small, a, b, grid, stream); break;
+        case Mode::DigestBf16State: launch_tiles<Mode::DigestBf16State>(small, a, b, grid, stream); break;
+        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

@@ -12,12 +12,14 @@ namespace pact {
 // table has to be allocated or copied.
 constexpr int kSegsPerLaunch = 32;
 
-// Threads per workgroup (4 waves of 64) and fp32 elements one thread moves
-// per tile: four 16-byte vectors per array.
+// Threads per workgroup (4 waves of 64).
 constexpr int kBlock = 256;
+
+// The stream probe's tile, the commit's: four 16-byte vectors of fp32 elements
+// per thread and array, 4096 elements.
 constexpr int kVec = 4;
 constexpr int kUnroll = 4;
-constexpr int kTile = kBlock * kVec * kUnroll;  // 4096 elements per tile
+constexpr int kTile = kBlock * kVec * kUnroll;
 
 // Digest partial sums: each result slot owns kLanes workspace lines of
 // kLaneStride words (256 bytes); a line begins with kNodesPerLane nodes of two
@@ -56,6 +58,7 @@ struct Batch {
     uint32_t nseg;
     uint32_t slot0;        // result slot of this batch's first segment
     uint32_t tile0;        // tiles of the call's earlier batches
+    uint32_t passes;       // passes of a tile
     uint32_t per_segment;  // nonzero: one result slot per segment, else one in all
     uint64_t tile_begin[kSegsPerLaunch + 1];
     uint64_t elem_begin[kSegsPerLaunch];  // shard-relative first element
@@ -95,16 +98,88 @@ enum class Mode : int {
     DigestBf16State = 6,
 };
 
+// A pass of a mode's tile kernel: `rows` rows of kBlock vectors of `vec`
+// elements.  A tile is Batch::passes of them, one after the other.
+struct Shape {
+    int vec, rows;
+    constexpr uint32_t elems() const { return (uint32_t)(kBlock * vec * rows); }
+};
+
+// The commits of binary32 state move one row of 4 KB per array (the comment at
+// kReserveLds in kernels.hip says why); the others' kernels, bound by reading or by
+// VALU issue, have more loads in flight per thread, and a second shape of one
+// short row for shards that would leave most of the GPU idle (small).
+constexpr Shape shape_of(Mode m, bool small) {
+    switch (m) {
+        case Mode::Commit:
+        case Mode::CommitZeroGrad:
+            return {4, 1};
+        case Mode::GradGuard:
+            return {4, 4};
+        case Mode::StateDigest:
+            return small ? Shape{4, 1} : Shape{4, 4};
+        case Mode::Bf16Digest:
+        case Mode::CommitBf16State:
+        case Mode::DigestBf16State:
+            return small ? Shape{4, 1} : Shape{8, 2};
+    }
+    return {4, 1};
+}
+
+// Elements up to which the small shape is the faster one (0: there is none).
+// us per call, small / large shape, at 0.1M, 1M, 4M and 16M elements:
+//   state digest  4.1 / 5.3   6.0 / 6.4  12.8 / 12.8  42.4 / 38.9
+//   bf16 digest   3.6 / 3.6   4.9 / 4.5   8.6 / 6.0   22.0 / 13.5
+//   BF16 commit   4.4 / 6.3   7.1 / 8.1  15.6 / 17.3  52.4 / 49.4
+//   BF16 digest   4.0 / 5.0   5.7 / 6.0  12.0 / 11.4  37.8 / 32.0
+constexpr uint64_t small_up_to(Mode m) {
+    switch (m) {
+        case Mode::StateDigest: return 3u << 20;
+        case Mode::Bf16Digest: return 1u << 19;
+        case Mode::CommitBf16State: return 6u << 20;
+        case Mode::DigestBf16State: return 3u << 19;
+        default: return 0;
+    }
+}
+
+// Consecutive tiles per XCD: a workgroup's XCD is its number modulo 8, so tiles
+// are dealt in groups of 8 * run, of which each XCD takes `run` neighbours.
+// Grids below `from` tiles keep their order.
+struct Runs {
+    uint32_t run, from;
+    uint32_t long_run, long_from;
+};
+constexpr uint32_t kXcds = 8;
+constexpr Runs runs_of(Mode m, bool small) {
+    constexpr uint32_t kNever = ~0u;
+    switch (m) {
+        case Mode::Commit:
+        case Mode::CommitZeroGrad:
+            // Of 128 KB per array, and 512 KB where that leaves 32 groups: us per
+            // commit in runs of 1 / 32 / 128 tiles: 83.7 / 79.8 / 83.2 at 16M
+            // elements, 163 / 154 / 152 at 32M, 395 / 368 / 361 at 76M.
+            return {32, 0, 128, 32768};
+        case Mode::StateDigest:
+            return {1, kNever, 1, kNever};  // bound by VALU issue: no difference
+        default:
+            // 16 tiles against 1: guard of 453M elements 288 -> 266 us, BF16
+            // digest 728 -> 720, BF16 commit 1237 -> 1225; below 8M elements
+            // up to 7% slower.
+            return small ? Runs{1, kNever, 1, kNever} : Runs{16, 2048, 16, kNever};
+    }
+}
+
 // Enqueue the clearing of what the tile kernels hand their shares in to: the
 // nodes of nres result slots when `words` is given, else the nslots digest slots.
 hipError_t launch_clear(uint64_t* digest, uint64_t* words, uint32_t nres, uint32_t nslots, hipStream_t stream);
 
-// Enqueue one batch in the given mode: one workgroup per tile, so `grid` is
-// the batch's tile count.
-hipError_t launch_batch(Mode mode, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream);
+// Enqueue one batch in the given mode, in tiles of shape_of(mode, small): one
+// workgroup per tile, so `grid` is the batch's tile count.
+hipError_t launch_batch(Mode mode, bool small, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream);
 
 // Enqueue one batch of a BF16-state mode (CommitBf16State, DigestBf16State).
-hipError_t launch_batch_bf16(Mode mode, const ArraysBf16& a, const Batch& b, uint32_t grid, hipStream_t stream);
+hipError_t launch_batch_bf16(Mode mode, bool small, const ArraysBf16& a, const Batch& b, uint32_t grid,
+                             hipStream_t stream);
 
 // Enqueue digest[nres] = sum of digest[0..nres).
 hipError_t launch_total(uint64_t* digest, uint32_t nres, hipStream_t stream);
