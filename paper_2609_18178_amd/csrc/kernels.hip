@@ -363,10 +363,16 @@ __device__ __forceinline__ void adamw_steps(float (&p)[N], const float (&m)[N], 
     for (int i = 0; i < N; ++i) in_range = in_range && sqrt_rn_in_range(v[i]);
     if (__builtin_amdgcn_ballot_w64(!in_range) == 0) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) p[i] = adamw_step<true>(p[i], m[i], v[i], s);
+        for (int i = 0; i < N; ++i) {
+            p[i] = adamw_step<true>(p[i], m[i], v[i], s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     } else {
 #pragma unroll
-        for (int i = 0; i < N; ++i) p[i] = adamw_step<false>(p[i], m[i], v[i], s);
+        for (int i = 0; i < N; ++i) {
+            p[i] = adamw_step<false>(p[i], m[i], v[i], s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
 }
 
@@ -387,6 +393,105 @@ __device__ __forceinline__ uint32_t to_bf16x2(float lo, float hi) {
 }
 
 __device__ __forceinline__ uint32_t to_bf16(float x) { return to_bf16x2(x, 0.0f) & 0xFFFFu; }
+__device__ __forceinline__ float widen_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float widen_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+
+// The larger, per half, of `most` and words * scale - from.
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2_t max_offset(u16x2_t most, uint32_t words, uint16_t scale, uint16_t from) {
+    const u16x2_t w = __builtin_bit_cast(u16x2_t, words);
+    return __builtin_elementwise_max(most, (u16x2_t)(w * scale - from));
+}
+__device__ __forceinline__ bool below(u16x2_t x, uint16_t limit) { return std::max(x.x, x.y) < limit; }
+
+// AdamW on a lane's 2 * N elements of one row of BF16 state, pairs of bf16 words.
+//
+// The exact step spends 19 of its instructions per element on a correctly rounded
+// square root and division, of which the rounding to bf16 keeps hardly anything.
+// So the step s = RN(step_size * RN(m / den)) is bracketed first: with the hardware's
+// root and reciprocal (each within one bit pattern of the correctly rounded one)
+//   s' = step_size * RN(m * rcp(RN(root' * rs_bc2 + eps))),
+// and unless something under- or overflows, s' and s differ by at most
+// 5 * 2^-24 (the roundings in s) + 8 * 2^-24 (two of 3 * 2^-24 and two of 2^-24 in s').
+// With 2^-24 for the rounding of step_size * (1 -+ 2^-20) that is less than 2^-20.
+// Rounding is monotone, to binary32 and on to bf16, so RN(p - s) lies between the two
+// fused p - RN(m * ..) * RN(step_size * (1 -+ 2^-20)), and where these round to the same
+// bf16 word that is the result.  Nothing under- or overflows to any effect if
+//   2^-40 <= step_size <= 2^40 and eps <= 2^100  (wave-uniform),
+//   2^-95 <= v < inf: den and its reciprocal are normal numbers;
+//   2^-50 <= |p'| < 2^20: as both ends round to one word, |s'| < 2^60, so that m / den
+//     does not overflow; what underflow adds to s is below 2^-108, no more than 2^-25
+//     of s' where |s'| >= 2^-83, and where |s'| is less both ends and RN(p - s) are p.
+// A NaN or an infinity anywhere leaves p' or v outside these ranges.  A row of a wave
+// with an element that fails takes the exact form.
+//
+// Bound by VALU issue and the clock it leaves: about 75 instructions per element
+// against 95 with the exact step.  453M elements 1195 -> 1104 us (5.7 TB/s), 76M 202 ->
+// 186, 6M 20.8 -> 19.0; fewer tiles in flight, 4 KB tiles and longer runs per XCD, which
+// the HBM-bound commits want, made no difference.
+template <int N>
+__device__ __forceinline__ void adamw_row_bf16(uint32_t (&P)[N], uint32_t (&G)[N], uint32_t (&M)[N],
+                                               uint32_t (&V)[N], const StepScalars& s) {
+    if (s.step_size >= 0x1p-40f && s.step_size <= 0x1p40f && s.eps <= 0x1p100f) {
+        constexpr uint16_t kVFrom = 0x1000, kVLimit = 0x7F80 - kVFrom;  // 2^-95 up to infinity
+        constexpr uint16_t kPFrom = 0x2680, kPLimit = 0x4980 - kPFrom;  // 2^-50 up to 2^20, signs shifted out
+        const float size_lo = s.step_size * (1.0f - 0x1p-20f), size_hi = s.step_size * (1.0f + 0x1p-20f);
+        u16x2_t v_most = {0, 0}, p_most = {0, 0};
+        uint32_t differ = 0;
+        uint32_t p_new[N], m_new[N], v_new[N];
+        auto ends = [&](float p, float g, float& m, float& v, float& near, float& far) {
+            adamw_moments(p, g, m, v, s);
+            const float den = __builtin_fmaf(__builtin_amdgcn_sqrtf(v), s.rs_bc2, s.eps);
+            const float ratio = m * __builtin_amdgcn_rcpf(den);
+            near = __builtin_fmaf(ratio, -size_lo, p);
+            far = __builtin_fmaf(ratio, -size_hi, p);
+        };
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            float near[2], far[2], m[2] = {widen_lo(M[i]), widen_hi(M[i])}, v[2] = {widen_lo(V[i]), widen_hi(V[i])};
+            ends(widen_lo(P[i]), widen_lo(G[i]), m[0], v[0], near[0], far[0]);
+            ends(widen_hi(P[i]), widen_hi(G[i]), m[1], v[1], near[1], far[1]);
+            p_new[i] = to_bf16x2(near[0], near[1]);
+            m_new[i] = to_bf16x2(m[0], m[1]);
+            v_new[i] = to_bf16x2(v[0], v[1]);
+            differ |= p_new[i] ^ to_bf16x2(far[0], far[1]);
+            p_most = max_offset(p_most, p_new[i], 2, 2 * kPFrom);
+            v_most = max_offset(v_most, v_new[i], 1, kVFrom);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const uint32_t fails = differ | (below(p_most, 2 * kPLimit) ? 0u : 1u) | (below(v_most, kVLimit) ? 0u : 1u);
+        if (__builtin_amdgcn_ballot_w64(fails != 0) == 0) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                P[i] = p_new[i];
+                M[i] = m_new[i];
+                V[i] = v_new[i];
+            }
+            return;
+        }
+    }
+    float p[2 * N], m[2 * N], v[2 * N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        // (opaque, or the moments from above are kept instead of formed again)
+        asm volatile("" : "+v"(P[i]), "+v"(G[i]), "+v"(M[i]), "+v"(V[i]));
+        p[2 * i] = widen_lo(P[i]);
+        p[2 * i + 1] = widen_hi(P[i]);
+        m[2 * i] = widen_lo(M[i]);
+        m[2 * i + 1] = widen_hi(M[i]);
+        v[2 * i] = widen_lo(V[i]);
+        v[2 * i + 1] = widen_hi(V[i]);
+        adamw_moments(p[2 * i], widen_lo(G[i]), m[2 * i], v[2 * i], s);
+        adamw_moments(p[2 * i + 1], widen_hi(G[i]), m[2 * i + 1], v[2 * i + 1], s);
+    }
+    adamw_steps<2 * N>(p, m, v, s);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        P[i] = to_bf16x2(p[2 * i], p[2 * i + 1]);
+        M[i] = to_bf16x2(m[2 * i], m[2 * i + 1]);
+        V[i] = to_bf16x2(v[2 * i], v[2 * i + 1]);
+    }
+}
 
 // ---------------------------------------------------------------------------
 // workgroup sum of a 64-bit value; result valid in thread 0
@@ -736,9 +841,6 @@ __device__ __forceinline__ uint64_t do_tile_vec(const Arrays& a, uint64_t e0, ui
 // BF16 state: vectors of Vec (eight or four) bf16 words per array; element 2j
 // of a vector is the low half of its word j.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float widen_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float widen_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-
 template <Mode M>
 __device__ __forceinline__ uint64_t do_scalar(const ArraysBf16& a, uint64_t e, const StepScalars& sc) {
     const uint64_t idx = a.goff + e;
@@ -758,76 +860,107 @@ __device__ __forceinline__ uint64_t do_scalar(const ArraysBf16& a, uint64_t e, c
     return hash_word<kTagP>(p, idx) + hash_word<kTagM>(m, idx) + hash_word<kTagV>(v, idx);
 }
 
-template <Mode M, typename Ix, int Vec, int Rows, bool Masked>
-__device__ __forceinline__ uint64_t do_tile_vec(const ArraysBf16& a, uint64_t e0, uint32_t nvec,
-                                                const StepScalars& sc) {
-    static_assert(!Masked || Rows == 1, "a masked tile is one row");
+template <Mode M, int Vec, int Rows, bool Masked>
+__device__ __forceinline__ uint64_t do_pass_bf16(const ArraysBf16& a, uint64_t e0, uint32_t nvec,
+                                                 const StepScalars& sc) {
+    static_assert(!Masked || Rows == 1, "a masked pass is one row");
     using W = Words16<Vec>;
+    constexpr int kN = Vec / 2;  // words of a vector
     constexpr uint32_t kRowBytes = kBlock * Vec * 2;
     const uint32_t lane = threadIdx.x * Vec * 2;
     const uint32_t bytes = Masked ? nvec * Vec * 2 : Rows * kRowBytes;
-    const Ix ix(a.goff + e0, threadIdx.x * Vec);  // word k of this lane: index + k
     const auto rp = tile_rsrc(a.p + e0, bytes);
     const auto rm = tile_rsrc(a.m + e0, bytes);
     const auto rv = tile_rsrc(a.v + e0, bytes);
-    typename W::type P[Rows], G[Rows], Mo[Rows], V[Rows];
+    uint32_t P[Rows][kN], G[Rows][kN], Mo[Rows][kN], V[Rows][kN];
+    auto load = [&](uint32_t (&x)[kN], __amdgpu_buffer_rsrc_t rsrc, int r) {
+        const auto w = W::load(rsrc, lane + r * kRowBytes);
+#pragma unroll
+        for (int j = 0; j < kN; ++j) x[j] = w[j];
+    };
+    auto store = [&](const uint32_t (&x)[kN], __amdgpu_buffer_rsrc_t rsrc, int r) {
+        typename W::type w;
+#pragma unroll
+        for (int j = 0; j < kN; ++j) w[j] = x[j];
+        W::store(w, rsrc, lane + r * kRowBytes);
+    };
 #pragma unroll
     for (int r = 0; r < Rows; ++r) {
-        P[r] = W::load(rp, lane + r * kRowBytes);
-        Mo[r] = W::load(rm, lane + r * kRowBytes);
-        V[r] = W::load(rv, lane + r * kRowBytes);
+        load(P[r], rp, r);
+        load(Mo[r], rm, r);
+        load(V[r], rv, r);
     }
     if constexpr (M == Mode::CommitBf16State) {
         const auto rg = tile_rsrc(a.g + e0, bytes);
 #pragma unroll
-        for (int r = 0; r < Rows; ++r) {
-            G[r] = W::load(rg, lane + r * kRowBytes);
-        }
-        constexpr int kN = Rows * Vec;
-        float p[kN], m[kN], v[kN];
+        for (int r = 0; r < Rows; ++r) load(G[r], rg, r);
 #pragma unroll
         for (int r = 0; r < Rows; ++r) {
-#pragma unroll
-            for (int j = 0; j < Vec / 2; ++j) {
-                const int i = r * Vec + 2 * j;
-                p[i] = widen_lo(P[r][j]);
-                p[i + 1] = widen_hi(P[r][j]);
-                m[i] = widen_lo(Mo[r][j]);
-                m[i + 1] = widen_hi(Mo[r][j]);
-                v[i] = widen_lo(V[r][j]);
-                v[i + 1] = widen_hi(V[r][j]);
-                adamw_moments(p[i], widen_lo(G[r][j]), m[i], v[i], sc);
-                adamw_moments(p[i + 1], widen_hi(G[r][j]), m[i + 1], v[i + 1], sc);
-            }
-        }
-        adamw_steps<kN>(p, m, v, sc);
-#pragma unroll
-        for (int r = 0; r < Rows; ++r) {
-#pragma unroll
-            for (int j = 0; j < Vec / 2; ++j) {
-                const int i = r * Vec + 2 * j;
-                P[r][j] = to_bf16x2(p[i], p[i + 1]);
-                Mo[r][j] = to_bf16x2(m[i], m[i + 1]);
-                V[r][j] = to_bf16x2(v[i], v[i + 1]);
-            }
-            W::store(P[r], rp, lane + r * kRowBytes);
-            W::store(Mo[r], rm, lane + r * kRowBytes);
-            W::store(V[r], rv, lane + r * kRowBytes);
+            adamw_row_bf16<kN>(P[r], G[r], Mo[r], V[r], sc);
+            store(P[r], rp, r);
+            store(Mo[r], rm, r);
+            store(V[r], rv, r);
         }
     }
-    uint64_t acc = 0;
+    const uint64_t first = a.goff + e0;
+    auto digest = [&](const auto& ix) {  // word k of this lane: index + k
+        uint64_t acc = 0;
 #pragma unroll
-    for (int r = 0; r < Rows; ++r) {
+        for (int r = 0; r < Rows; ++r) {
 #pragma unroll
-        for (int j = 0; j < Vec / 2; ++j) {
-            const uint32_t o = r * kBlock * Vec + 2 * j;
-            acc += ix.template hash<kTagP>(P[r][j] & 0xFFFFu, o) + ix.template hash<kTagP>(P[r][j] >> 16, o + 1) +
-                   ix.template hash<kTagM>(Mo[r][j] & 0xFFFFu, o) + ix.template hash<kTagM>(Mo[r][j] >> 16, o + 1) +
-                   ix.template hash<kTagV>(V[r][j] & 0xFFFFu, o) + ix.template hash<kTagV>(V[r][j] >> 16, o + 1);
-            if constexpr (Masked) __builtin_amdgcn_sched_barrier(0);
+            for (int j = 0; j < kN; ++j) {
+                const uint32_t o = r * kBlock * Vec + 2 * j;
+                // (opaque, or the halves of all words are taken apart, and kept, before
+                // the branch on the index form)
+                uint32_t p = P[r][j], m = Mo[r][j], v = V[r][j];
+                asm volatile("" : "+v"(p), "+v"(m), "+v"(v));
+                acc += ix.template hash<kTagP>(p & 0xFFFFu, o) + ix.template hash<kTagP>(p >> 16, o + 1) +
+                       ix.template hash<kTagM>(m & 0xFFFFu, o) + ix.template hash<kTagM>(m >> 16, o + 1) +
+                       ix.template hash<kTagV>(v & 0xFFFFu, o) + ix.template hash<kTagV>(v >> 16, o + 1);
+                if constexpr (Masked) __builtin_amdgcn_sched_barrier(0);
+            }
         }
+        return acc;
+    };
+    if constexpr (Masked) {
+        const uint64_t acc = digest(IndexAny(first, threadIdx.x * Vec));
+        return threadIdx.x >= nvec ? 0 : acc;
+    } else {
+        constexpr uint32_t kPass = kBlock * Vec * Rows;
+        if (IndexLo16::applies(first, kPass)) return digest(IndexLo16(first, threadIdx.x * Vec));
+        if (same_high_half(first, kPass)) return digest(IndexHi32(first, threadIdx.x * Vec));
+        return digest(IndexAny(first, threadIdx.x * Vec));
     }
-    return Masked && threadIdx.x >= nvec ? 0 : acc;
+}
+
+// The whole pass, whatever index form it takes, and one row of whole vectors.
+template <Mode M, int Vec, int Rows>
+__device__ __forceinline__ uint64_t do_pass(const ArraysBf16& a, uint64_t e0, const StepScalars& sc) {
+    return do_pass_bf16<M, Vec, Rows, false>(a, e0, 0, sc);
+}
+template <Mode M, int Vec>
+__device__ __forceinline__ uint64_t do_row(const ArraysBf16& a, uint64_t e0, uint32_t nvec, const StepScalars& sc) {
+    return do_pass_bf16<M, Vec, 1, true>(a, e0, nvec, sc);
+}
+template <Mode M, int Vec, int Rows>
+__device__ __forceinline__ uint64_t do_pass(const Arrays& a, uint64_t e0, const StepScalars& sc) {
+    constexpr uint32_t kPass = kBlock * Vec * Rows;
+    // The short index form for passes that do not cross a multiple of
+    // 2^32 (a uniform branch: at most one in 2^20 takes the other);
+    // the binary32 commits are bound by HBM, not by VALU issue, and keep
+    // the plain form (the short one measured 0.3% slower there, with one
+    // more wave per SIMD resident).
+    if (kWords16<M> && IndexLo16::applies(a.goff + e0, kPass)) {
+        return do_tile_vec<M, IndexLo16, Vec, Rows, false>(a, e0, 0, sc);
+    }
+    if (!kCommits<M> && same_high_half(a.goff + e0, kPass)) {
+        return do_tile_vec<M, IndexHi32, Vec, Rows, false>(a, e0, 0, sc);
+    }
+    return do_tile_vec<M, IndexAny, Vec, Rows, false>(a, e0, 0, sc);
+}
+template <Mode M, int Vec>
+__device__ __forceinline__ uint64_t do_row(const Arrays& a, uint64_t e0, uint32_t nvec, const StepScalars& sc) {
+    return do_tile_vec<M, IndexAny, Vec, 1, true>(a, e0, nvec, sc);
 }
 
 // ---------------------------------------------------------------------------
@@ -892,20 +1025,7 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
     } else {
         const uint64_t left = e0 < seg_end ? seg_end - e0 : 0;
         const uint32_t whole = left < tile_elems ? (uint32_t)left / kPass : passes;  // the tile's whole passes
-        auto one_pass = [&](uint64_t at) {
-            // The short index form for passes that do not cross a multiple of
-            // 2^32 (a uniform branch: at most one in 2^20 takes the other);
-            // the binary32 commits are bound by HBM, not by VALU issue, and keep
-            // the plain form (the short one measured 0.3% slower there, with one
-            // more wave per SIMD resident).
-            if (kWords16<M> && IndexLo16::applies(a.goff + at, kPass)) {
-                acc += do_tile_vec<M, IndexLo16, kVecs, kRows, false>(a, at, 0, sc);
-            } else if (!kCommits<M> && same_high_half(a.goff + at, kPass)) {
-                acc += do_tile_vec<M, IndexHi32, kVecs, kRows, false>(a, at, 0, sc);
-            } else {
-                acc += do_tile_vec<M, IndexAny, kVecs, kRows, false>(a, at, 0, sc);
-            }
-        };
+        auto one_pass = [&](uint64_t at) { acc += do_pass<M, kVecs, kRows>(a, at, sc); };
         if constexpr (kManyPasses<M> && !Small) {
 #pragma unroll 1
             for (uint32_t pass = 0; pass < whole; ++pass) one_pass(uniform(e0 + pass * kPass));
@@ -922,7 +1042,7 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
             const uint32_t nvec = (uint32_t)(seg_end - at) / kVecs;
 #pragma unroll 1
             for (uint32_t done = 0; done < nvec; done += kBlock) {
-                acc += do_tile_vec<M, IndexAny, kVecs, 1, true>(a, at + done * kVecs, nvec - done, sc);
+                acc += do_row<M, kVecs>(a, at + done * kVecs, nvec - done, sc);
             }
             e = at + nvec * kVecs + threadIdx.x;
             e_end = seg_end;
@@ -976,23 +1096,23 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
 // Waves per SIMD a kernel must be able to keep resident (caps its VGPRs).
 // The two standalone digests are bound by VALU issue and keep the full
 // eight waves per SIMD (the short index form would otherwise take the state
-// digest to 66 VGPRs and seven waves).  The BF16-state commit, which holds
-// the moments of all its elements before the square roots, needs at least
-// five; it takes 79 VGPRs, six waves (capped at seven it spills).
-template <Mode M>
+// digest to 66 VGPRs and seven waves).  The BF16-state commit takes 64 VGPRs in
+// either case, scheduled for eight waves in its small shape (6M elements 18.6 us
+// against 19.6) and for six in the large one (453M 1115 us against 1128).
+template <Mode M, bool Small>
 constexpr unsigned kMinWavesPerSimd = (M == Mode::StateDigest || M == Mode::DigestBf16State) ? 8u
-                                      : (M == Mode::CommitBf16State)                         ? 6u
+                                      : (M == Mode::CommitBf16State)                         ? (Small ? 8u : 6u)
                                                                                              : 1u;
 
 template <Mode M, bool Small>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWavesPerSimd<M>)))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWavesPerSimd<M, Small>)))
 void tile_kernel(Arrays a, Batch bt) {
     __shared__ uint64_t lds[kBlock / 64];
     tile_body<M, Small>(a, bt, lds);
 }
 
 template <Mode M, bool Small>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWavesPerSimd<M>)))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWavesPerSimd<M, Small>)))
 void tile_kernel_bf16(ArraysBf16 a, Batch bt) {
     __shared__ uint64_t lds[kBlock / 64];
     tile_body<M, Small>(a, bt, lds);
