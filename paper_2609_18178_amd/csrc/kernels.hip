@@ -3,13 +3,13 @@
 // One tile kernel serves every mode on binary32 state (commit, commit that
 // also zeroes the gradient, state digest, bf16 digest, gradient guard) and a
 // twin serves state held in BF16 (commit, state digest).
-// Work is cut into tiles of kTile elements that never straddle a segment, and
+// Work is cut into tiles that never straddle a segment, and
 // each workgroup takes exactly one tile (the hardware dispatcher then keeps
 // every CU full and balances the tail by itself; a persistent grid measured
 // slower on this pattern).  A full, aligned tile moves, per thread and per
-// binary32 array, four 16-byte vectors with buffer_load/store_dwordx4, and four
-// 8-byte ones into the bf16 working copy (dwordx2); on BF16 state, two 16-byte
-// vectors of eight elements per array.  All of it is marked non-temporal.  A
+// array, one to four 16-byte vectors with buffer_load/store_dwordx4 (shape_of in
+// launch.h), and as many 8-byte ones into the bf16 working copy (dwordx2).  All of
+// it is marked non-temporal.  A
 // segment's tiles begin at its first element that is aligned in every array
 // (up to seven elements in), and a last tile that is not full masks its
 // vectors; only the elements before the first and behind the last vector, and
@@ -964,24 +964,39 @@ __device__ __forceinline__ uint64_t do_row(const Arrays& a, uint64_t e0, uint32_
 }
 
 // ---------------------------------------------------------------------------
-// One workgroup per tile.  The tile's segment is found by binary search over
-// the batch's tile prefix (kernel arguments, scalar loads); the tile's digest
-// share is summed over the workgroup in LDS and added with one 64-bit atomic.
+// One workgroup per tile.  The tile's segment comes from the batch's tables
+// (kernel arguments, scalar loads); the tile's digest share is summed over the
+// workgroup in LDS and handed in with a 64-bit atomic for each of two words.
 // ---------------------------------------------------------------------------
 // The tile of this block, with runs of `run` tiles per XCD; the blocks behind
 // the last whole group keep their order.
-__device__ __forceinline__ uint32_t dealt_tile(uint32_t run) {
+__device__ __forceinline__ uint32_t dealt_tile(uint32_t tiles, uint32_t run) {
     const uint32_t group = kXcds * run;
     const uint32_t r = blockIdx.x % group, first = blockIdx.x - r;
-    return gridDim.x - first >= group ? first + r % kXcds * run + r / kXcds : blockIdx.x;
+    return tiles - first >= group ? first + r % kXcds * run + r / kXcds : blockIdx.x;
 }
 
 template <Mode M, bool Small>
-__device__ __forceinline__ uint32_t tile_of_block() {
+__device__ __forceinline__ uint32_t tile_of_block(uint32_t tiles) {
     constexpr Runs kRuns = runs_of(M, Small);
-    if (gridDim.x >= kRuns.long_from) return dealt_tile(kRuns.long_run);
-    if (gridDim.x >= kRuns.from) return dealt_tile(kRuns.run);
+    if (tiles >= kRuns.long_from) return dealt_tile(tiles, kRuns.long_run);
+    if (tiles >= kRuns.from) return dealt_tile(tiles, kRuns.run);
     return blockIdx.x;
+}
+
+// Has the compiler load what a workgroup needs of the arguments here, in one go:
+// it would rather load each where it is used, and the workgroup wait each time.
+__device__ __forceinline__ void load_now(Segment& s) {
+    asm volatile(""
+                 : "+s"(s.elem_begin), "+s"(s.elem_count), "+s"(s.tile_begin), "+s"(s.tile_end), "+s"(s.align),
+                   "+s"(s.sc.beta1), "+s"(s.sc.beta2), "+s"(s.sc.eps), "+s"(s.sc.decay), "+s"(s.sc.omb1),
+                   "+s"(s.sc.omb2), "+s"(s.sc.step_size), "+s"(s.sc.rs_bc2));
+}
+__device__ __forceinline__ void load_now(const Arrays& a) {
+    asm volatile("" ::"s"(a.p), "s"(a.g), "s"(a.m), "s"(a.v), "s"(a.b), "s"(a.goff));
+}
+__device__ __forceinline__ void load_now(const ArraysBf16& a) {
+    asm volatile("" ::"s"(a.p), "s"(a.g), "s"(a.m), "s"(a.v), "s"(a.goff));
 }
 
 template <Mode M, bool Small, typename A>
@@ -991,23 +1006,32 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
     constexpr uint32_t kPass = kShape.elems();
     const uint32_t passes = kManyPasses<M> && !Small ? bt.passes : 1;
     const uint32_t tile_elems = kPass * passes;
-    const uint64_t tile = tile_of_block<M, Small>();
-    uint32_t lo = 0, hi = bt.nseg;  // largest lo with tile_begin[lo] <= tile
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (tile >= bt.tile_begin[mid]) {
-            lo = mid;
-        } else {
-            hi = mid;
+    // The tile's segment.  Segment 0's line is loaded together with the number of
+    // segments, so what a flat shard needs is there after one wait; else the segment
+    // is counted out from all tile_begin at once (a binary search waits five times,
+    // each time for memory in the first workgroups of a launch).  Against such a search
+    // over a table per field: commit of 0.1M and 1M elements 4.95 -> 4.65 and 8.0 -> 7.6 us,
+    // guard of 1M 4.5 -> 4.0, commit of 143M in 291 segments 737 -> 732.
+    Segment sg = bt.seg[0];
+    uint32_t seg = 0, nseg = bt.nseg, tiles = bt.tiles;
+    load_now(a);
+    asm volatile("" : "+s"(nseg), "+s"(tiles));
+    load_now(sg);
+    const uint32_t tile = tile_of_block<M, Small>(tiles);
+    if (nseg > 1) {
+#pragma unroll
+        for (int k = 1; k < kSegsPerLaunch; ++k) {
+            // (two scalar instructions; the compiler takes five and goes through VGPRs)
+            asm("s_cmp_ge_u32 %1, %2\n\ts_addc_u32 %0, %0, 0" : "+s"(seg) : "s"(tile), "s"(bt.tile_begin[k]) : "scc");
         }
+        sg = bt.seg[seg];
+        load_now(sg);
     }
-    const uint32_t seg = lo;
-    const StepScalars sc = bt.sc[seg];
-    const uint64_t seg_first = bt.elem_begin[seg];
-    const uint64_t seg_end = seg_first + bt.elem_count[seg];
-    const uint32_t align = bt.align[seg];
-    const uint64_t e0 = seg_first + (align == kNeverAligned ? 0 : align) +
-                        (tile - bt.tile_begin[seg]) * (uint64_t)tile_elems;
+    const StepScalars& sc = sg.sc;
+    const uint64_t seg_first = sg.elem_begin;
+    const uint64_t seg_end = seg_first + sg.elem_count;
+    const uint32_t align = sg.align;
+    const uint64_t e0 = seg_first + (align == kNeverAligned ? 0 : align) + (tile - sg.tile_begin) * (uint64_t)tile_elems;
     // This wave's word of the workgroup sum starts at zero (LDS operations of
     // one wave are carried out in the order it issues them, so the clearing
     // comes before the wave's own additions below).
@@ -1047,7 +1071,7 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
             e = at + nvec * kVecs + threadIdx.x;
             e_end = seg_end;
         }
-        if (tile == bt.tile_begin[seg] && threadIdx.x >= 64) {
+        if (tile == sg.tile_begin && threadIdx.x >= 64) {
             // The first tile's second wave: the elements before the first
             // aligned one (the segment may end among them).
             e = seg_first + threadIdx.x - 64;
@@ -1065,7 +1089,7 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
     __hip_atomic_fetch_add(wave_sum, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __syncthreads();
     const uint32_t slot = bt.per_segment ? bt.slot0 + seg : 0;
-    const uint32_t in_seg = uniform((uint32_t)(tile - bt.tile_begin[seg]));
+    const uint32_t in_seg = tile - sg.tile_begin;
     // wave 0 for the slot, wave 1 for the total, whose nodes sit beside slot 0's
     const uint32_t wave = uniform(threadIdx.x >> 6);
     const bool total = wave == 1;
@@ -1080,12 +1104,12 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
                 atomicAdd(reinterpret_cast<unsigned long long*>(a.res.digest + slot), (unsigned long long)s);
             }
         } else if ((threadIdx.x & 63) < 2) {
-            const uint32_t n = uniform((uint32_t)(bt.tile_begin[seg + 1] - bt.tile_begin[seg]));
+            const uint32_t n = sg.tile_end - sg.tile_begin;
             uint64_t* const line0 = a.res.words + a.res.set * 2;
             uint64_t* const line = line0 + (uint64_t)slot * kLanes * kLaneStride;
             hand_in(total ? line0 + 8 : line, total ? line0 + kLaneStride + 4 : line + 4,
                     a.res.digest + (total ? a.res.total_slot : slot), total ? a.res.total_tiles : n,
-                    total ? bt.tile0 + uniform((uint32_t)tile) : in_seg, s);
+                    total ? bt.tile0 + tile : in_seg, s);
         }
     }
     if (a.res.words != nullptr && in_seg == 0) {

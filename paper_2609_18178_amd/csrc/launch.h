@@ -50,21 +50,29 @@ struct StepScalars {
 // (bf16 copy) aligned at the same element.
 constexpr uint32_t kNeverAligned = ~0u;
 
-// One launch's slice of the segment table.  Tiles never straddle segments:
-// segment s owns tiles [tile_begin[s], tile_begin[s+1]), at
-// least one (an empty segment's tile hands in a share of zero); they cover its
-// elements from the first aligned one on, and the first tile those before it.
+// One segment of a launch: a line of 64 bytes, so that a tile's workgroup waits
+// for one.  It owns the tiles [tile_begin, tile_end), at least one (an empty
+// segment's tile hands in a share of zero): they cover its elements from the first
+// aligned one on, and the first tile those before it.
+struct alignas(64) Segment {
+    uint64_t elem_begin;  // shard-relative first element
+    uint64_t elem_count;
+    uint32_t tile_begin, tile_end;
+    uint32_t align;  // elements before the first aligned one, or kNeverAligned
+    StepScalars sc;
+};
+static_assert(sizeof(Segment) == 64, "one line");
+
+// One launch's slice of the segment table.  Tiles never straddle segments.
 struct Batch {
     uint32_t nseg;
     uint32_t slot0;        // result slot of this batch's first segment
     uint32_t tile0;        // tiles of the call's earlier batches
+    uint32_t tiles;        // of this batch
     uint32_t passes;       // passes of a tile
     uint32_t per_segment;  // nonzero: one result slot per segment, else one in all
-    uint64_t tile_begin[kSegsPerLaunch + 1];
-    uint64_t elem_begin[kSegsPerLaunch];  // shard-relative first element
-    uint64_t elem_count[kSegsPerLaunch];
-    uint32_t align[kSegsPerLaunch];       // elements before the first aligned one, or kNeverAligned
-    StepScalars sc[kSegsPerLaunch];
+    alignas(64) uint32_t tile_begin[kSegsPerLaunch];  // the segments', ~0 behind the last
+    Segment seg[kSegsPerLaunch];
 };
 
 struct Arrays {

@@ -465,15 +465,18 @@ int run(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, ui
             const uint32_t align = align_of(mode, s, w.first);
             const uint64_t n = tiles_of(w.count, align, t.elems);
             if (tiles + n > kMaxTiles) break;
-            b.tile_begin[cnt] = tiles;
+            pact::Segment& sg = b.seg[cnt];
+            sg.tile_begin = b.tile_begin[cnt] = (uint32_t)tiles;
             tiles += n;
-            b.elem_begin[cnt] = w.first;
-            b.elem_count[cnt] = w.count;
-            b.sc[cnt] = w.sc;
-            b.align[cnt] = align;
+            sg.tile_end = (uint32_t)tiles;
+            sg.elem_begin = w.first;
+            sg.elem_count = w.count;
+            sg.sc = w.sc;
+            sg.align = align;
         }
         b.nseg = (uint32_t)cnt;
-        b.tile_begin[cnt] = tiles;
+        b.tiles = (uint32_t)tiles;
+        std::fill(b.tile_begin + cnt, b.tile_begin + pact::kSegsPerLaunch, ~0u);
         e = is_bf16_state(mode) ? pact::launch_batch_bf16(mode, t.small, ab, b, (uint32_t)tiles, stream)
                                 : pact::launch_batch(mode, t.small, a, b, (uint32_t)tiles, stream);
         if (e != hipSuccess) return fail_hip(e);
