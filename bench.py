@@ -73,7 +73,7 @@ def parse():
     return ap.parse_args()
 
 
-COMMIT_KERNEL = "tile_kernel<(pact::Mode)0>"
+COMMIT_KERNEL = "tile_kernel<(pact::Mode)0"
 PROBE_KERNEL = "probe_kernel("
 
 
@@ -236,11 +236,13 @@ def _cpu_model() -> str:
     return "unknown"
 
 
-# rocprofv3 kernel names -> the names bench.py reports them under
-CLOCK_KERNELS = (("tile_kernel<(pact::Mode)0>", "commit", 30), ("probe_kernel(", "probe", 30),
-                 ("tile_kernel<(pact::Mode)3>", "commit_zero_grad", 34), ("tile_kernel<(pact::Mode)4>", "grad_guard", 4),
-                 ("tile_kernel<(pact::Mode)1>", "shard_digest", 12),
-                 ("tile_kernel_bf16<(pact::Mode)5>", "commit_bf16_state", 14))
+# rocprofv3 kernel names -> the names bench.py reports them under, bytes per
+# element, and elements of a workgroup (one tile) on a large shard
+CLOCK_KERNELS = (("tile_kernel<(pact::Mode)0", "commit", 30, 1024), ("probe_kernel(", "probe", 30, 4096),
+                 ("tile_kernel<(pact::Mode)3", "commit_zero_grad", 34, 1024),
+                 ("tile_kernel<(pact::Mode)4", "grad_guard", 4, 4096),
+                 ("tile_kernel<(pact::Mode)1", "shard_digest", 12, 4096),
+                 ("tile_kernel_bf16<(pact::Mode)5", "commit_bf16_state", 14, 4096))
 XCDS = 8      # GRBM_GUI_ACTIVE comes back summed over the eight XCDs
 NUM_CUS = 256
 # Nominal VALU issue peak: 256 CUs x 4 SIMDs, each SIMD 16 lanes wide, so one
@@ -259,12 +261,14 @@ def record_clock(workload: str, clock_csv: str) -> dict:
     import workloads as wl
 
     n = wl.WORKLOADS[workload].numel
-    full_grid = -(-n // 4096) * 256  # work-items of one full-shard launch (one 256-thread workgroup per tile)
     disp = {}
     with open(clock_csv) as f:
         for row in csv.DictReader(f):
-            hit = [(key, bpe) for pat, key, bpe in CLOCK_KERNELS if pat in row["Kernel_Name"]]
-            if not hit or int(row.get("Grid_Size", full_grid)) != full_grid:
+            hit = [(key, bpe, tile) for pat, key, bpe, tile in CLOCK_KERNELS if pat in row["Kernel_Name"]]
+            if not hit:
+                continue
+            full_grid = -(-n // hit[0][2]) * 256  # work-items of one full-shard launch (256 threads per tile)
+            if int(row.get("Grid_Size", full_grid)) != full_grid:
                 continue  # other kernels, and the sub-shard launches of the VALU-ceiling timing
             d = disp.setdefault(int(row["Dispatch_Id"]), {"key": hit[0][0], "bpe": hit[0][1]})
             d[row["Counter_Name"]] = float(row["Counter_Value"])
@@ -742,8 +746,8 @@ def main():
             # the same 30 B/element pattern with no arithmetic, in the same run:
             # the practical ceiling of the access pattern (context, not the metric)
             "frac_of_probe": (achieved / probe_res["gbps"]) if probe_res else None,
-            "timing": "hipEvents around each commit call on the launch stream; a call also runs the "
-                      "one-workgroup kernels that clear and sum the digest lanes (a few microseconds)",
+            "timing": "hipEvents around each commit call on the launch stream; a call is its tile launches alone "
+                      "(one per 32 segments), whose last workgroup writes the digest",
         },
         "cpu_baseline": cpu,
         "parity": parity,
