@@ -199,15 +199,39 @@ def _dev_tensor(t: Optional[torch.Tensor], dtype, name: str, n: int, device: Opt
 class _Workspace:
     """The digest workspace of a shard and what is known about it between
     calls (``pact_workspace_state``): the library skips clearing a workspace
-    that its last call, on the same stream, left clear."""
+    that its last call, on the same stream, left clear.
+
+    The workspace is scratch that the caller may read, write or replace.  As long
+    as nobody has asked for it, nobody but the library's calls can have written
+    to it.  From then on anyone may, at any time, and the calls that only read
+    the shard and the BF16 commit have it cleared first; the binary32 commits
+    go by ``workspace_clean``."""
 
     def _init_workspace(self, nbytes: Optional[int]) -> None:
         self.workspace = None
-        self._ws_state = _CWorkspaceState()
         if nbytes is not None:
-            self.workspace = torch.zeros(nbytes, dtype=torch.uint8, device=self.device)
+            self._workspace = torch.zeros(nbytes, dtype=torch.uint8, device=self.device)
+            self._ws_shared = False
             self._ws_state.stream = torch.cuda.current_stream(self.device).cuda_stream or 0
             self._ws_state.clear = 1
+
+    @property
+    def workspace(self) -> Optional[torch.Tensor]:
+        """The device scratch of the shard's calls (None: they do without)."""
+        self._ws_shared = True
+        return self._workspace
+
+    @workspace.setter
+    def workspace(self, value: Optional[torch.Tensor]) -> None:
+        self._workspace = value
+        self._ws_shared = True
+        self._ws_state = _CWorkspaceState()  # nothing is known about this one
+
+    def _known_state(self) -> _CWorkspaceState:
+        """The state for a call that takes nobody's word about the workspace."""
+        if self._ws_shared:
+            self._ws_state.clear = 0
+        return self._ws_state
 
     def _tables(self):
         """num_segs' neighbours in the packed shard: segs, num_segs, num_hypers, hypers."""
@@ -217,14 +241,14 @@ class _Workspace:
 
     def _results(self, workspace: bool):
         """The end of the packed shard: digest_dev, workspace, workspace_bytes, stream."""
-        ws = self.workspace if workspace else None
+        ws = self._workspace if workspace else None
         at, nbytes = (0, 0) if ws is None else (ws.data_ptr(), ws.numel())
         return self.digest.data_ptr(), at, nbytes, torch._C._cuda_getCurrentRawStream(self.device.index)
 
     @property
     def workspace_clean(self) -> bool:
-        """Whether the workspace is clear for the next call; set False after
-        writing to it by other means."""
+        """Whether the next binary32 commit may take the workspace to be clear; set
+        False after writing to it by other means."""
         return bool(self._ws_state.clear)
 
     @workspace_clean.setter
@@ -287,7 +311,7 @@ class Shard(_Workspace):
             s.hypers = ctypes.cast(self._chypers, ctypes.POINTER(_CHyper))
             s.num_hypers = len(self.hypers)
         s.digest_dev = (digest_out if digest_out is not None else self.digest).data_ptr()
-        ws = getattr(self, "workspace", None) if workspace else None
+        ws = getattr(self, "_workspace", None) if workspace else None
         if ws is not None:
             s.workspace, s.workspace_bytes = ws.data_ptr(), ws.numel()
         s.stream = torch.cuda.current_stream(self.device).cuda_stream
@@ -346,7 +370,7 @@ class ShardBf16(_Workspace):
             s.hypers = ctypes.cast(self._chypers, ctypes.POINTER(_CHyper))
             s.num_hypers = len(self.hypers)
         s.digest_dev = self.digest.data_ptr()
-        ws = getattr(self, "workspace", None)
+        ws = getattr(self, "_workspace", None)
         if ws is not None:
             s.workspace, s.workspace_bytes = ws.data_ptr(), ws.numel()
         s.stream = torch.cuda.current_stream(self.device).cuda_stream
@@ -487,13 +511,13 @@ def adamw_commit_static(shard: Shard, step: int, hyper: Optional[Hyper] = None,
 
 def adamw_commit_bf16(shard: ShardBf16, step: int, hyper: Optional[Hyper] = None) -> torch.Tensor:
     """Commit one AdamW step on BF16 state (in place) and digest the result."""
-    _enqueue(shard, "adamw_commit_bf16_ws", shard._packed(), int(step), _hyper(shard, hyper), shard._ws_state)
+    _enqueue(shard, "adamw_commit_bf16_ws", shard._packed(), int(step), _hyper(shard, hyper), shard._known_state())
     return shard.digest
 
 
 def shard_digest_bf16(shard: ShardBf16) -> torch.Tensor:
     """Digest of the current BF16 (param, exp_avg, exp_avg_sq)."""
-    _enqueue(shard, "shard_digest_bf16_ws", shard._packed(), shard._ws_state)
+    _enqueue(shard, "shard_digest_bf16_ws", shard._packed(), shard._known_state())
     return shard.digest
 
 
@@ -515,20 +539,20 @@ def _result_slots(shard, out: Optional[torch.Tensor]) -> torch.Tensor:
 def grad_guard(shard: Shard, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Count the gradient elements that are not +0.0 (per segment and total)."""
     out = _result_slots(shard, out)
-    _enqueue(shard, "grad_guard_ws", shard._packed(), out.data_ptr(), shard._ws_state)
+    _enqueue(shard, "grad_guard_ws", shard._packed(), out.data_ptr(), shard._known_state())
     return out
 
 
 def shard_digest(shard: Shard) -> torch.Tensor:
     """Digest of the shard's current (param, exp_avg, exp_avg_sq)."""
-    _enqueue(shard, "shard_digest_ws", shard._packed(), shard._ws_state)
+    _enqueue(shard, "shard_digest_ws", shard._packed(), shard._known_state())
     return shard.digest
 
 
 def bf16_digest(shard: Shard, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Digest (tag 3) of the bf16 copy, into ``out`` (allocated if None)."""
     out = _result_slots(shard, out)
-    _enqueue(shard, "bf16_digest_ws", shard._packed(), out.data_ptr(), shard._ws_state)
+    _enqueue(shard, "bf16_digest_ws", shard._packed(), out.data_ptr(), shard._known_state())
     return out
 
 

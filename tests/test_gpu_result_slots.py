@@ -135,3 +135,54 @@ def test_digest_replays_from_a_hip_graph():
         assert pk.to_u64(pk.grad_guard(sh)) == [int(np.count_nonzero(g.view(np.uint32)))]
         sh.digest.fill_(-1)
         assert pk.to_u64(pk.shard_digest(sh)) == want
+
+
+def _reads(pk, sh, p, g, m, v, goff):
+    """(call, its result slots) of the calls that only read a shard."""
+    b = host_copy(sh)
+    return [(lambda: pk.shard_digest(sh), [oracle.state_digest(p, m, v, goff)]),
+            (lambda: pk.grad_guard(sh), [int(np.count_nonzero(g.view(np.uint32)))]),
+            (lambda: pk.bf16_digest(sh), [oracle.bf16_digest(b, goff)])]
+
+
+def host_copy(sh):
+    return sh.param_bf16.cpu().numpy().view(np.uint16)
+
+
+@pytest.mark.parametrize("n", [3 * T + 7, 70 * T])
+@pytest.mark.parametrize("how", ["written", "written later", "replaced"])
+def test_reads_after_the_caller_wrote_to_the_workspace(n, how):
+    """The workspace is the caller's scratch: whatever was written to it by other
+    means, without a word to the shard, the digests, the guard and the BF16
+    commit are right (the slots hold something else before each call)."""
+    import torch
+
+    pk = _pk()
+    p, g, m, v = _state(n, 6)
+
+    def dirty(sh, kept):
+        if how == "replaced":
+            sh.workspace = torch.full_like(sh.workspace, 0x5A)
+        elif how == "written":
+            sh.workspace.fill_(0x5A)
+        else:
+            kept.fill_(0x5A)
+        sh.digest.fill_(-1)
+
+    sh = make_shard(p, g, m, v, 11)
+    kept = sh.workspace
+    for _ in range(2):
+        for call, want in _reads(pk, sh, p, g, m, v, 11):
+            dirty(sh, kept)
+            assert pk.to_u64(call()) == want
+            assert pk.to_u64(call()) == want
+    words = [oracle.bf16_rne_bits(x.view(np.uint32)) for x in (p, g, m, v)]
+    sh = pk.ShardBf16(*(torch.from_numpy(x.view(np.int16).copy()).cuda() for x in words), 11)
+    kept = sh.workspace
+    p, g, m, v = words
+    for step in (3, 4):
+        dirty(sh, kept)
+        want = oracle.commit_and_digest_bf16(p, g, m, v, o_hyper(H), step, 11)
+        assert pk.to_u64(pk.adamw_commit_bf16(sh, step, pk.Hyper(**H))) == [want]
+        dirty(sh, kept)
+        assert pk.to_u64(pk.shard_digest_bf16(sh)) == [want]

@@ -1,4 +1,5 @@
-"""The bytes the Python calls hand to the library are the C structures' (no GPU)."""
+"""What the Python calls hand to the library: the C structures as bytes, and what is
+known about the workspace (no GPU)."""
 import ctypes
 
 import pytest
@@ -44,3 +45,40 @@ def test_the_other_kind_of_shard_is_refused(monkeypatch, call, cls):
     sh = _shard(monkeypatch, cls, None, False)
     with pytest.raises(ctypes.ArgumentError):
         call(sh, 1) if "commit" in call.__name__ else call(sh)
+
+
+@pytest.mark.parametrize("cls", [pk.Shard, pk.ShardBf16])
+@pytest.mark.parametrize("how", ["asked for", "replaced"])
+def test_a_workspace_that_others_may_write_to_is_not_taken_to_be_clear(monkeypatch, cls, how):
+    """Once the caller has had the workspace, or put another in its place, only a binary32
+    commit goes by what its last call left."""
+    monkeypatch.setattr(pk._Workspace, "_init_workspace", lambda self, nbytes: None)
+    sh = _shard(monkeypatch, cls, None, False)
+    sh.workspace = torch.zeros(16 * 32 * 8, dtype=torch.uint8)
+    sh._ws_shared, sh._ws_state.clear = False, 1  # as a shard that made its own
+    seen = []
+
+    def entry(shard, name, packed, *args):
+        seen.append(args[-1].clear)
+        args[-1].clear = 1  # as a call that ran
+
+    monkeypatch.setattr(pk, "_enqueue", entry)
+    out = torch.zeros(1, dtype=torch.int64)
+    monkeypatch.setattr(pk, "_result_slots", lambda shard, o: out)
+    reads = [pk.shard_digest, pk.grad_guard, pk.bf16_digest] if cls is pk.Shard else \
+        [pk.shard_digest_bf16, lambda s: pk.adamw_commit_bf16(s, 1)]
+    for call in reads:
+        call(sh)
+    assert seen == [1] * len(reads)
+    if how == "asked for":
+        assert sh.workspace.numel() == 16 * 32 * 8
+    else:
+        sh.workspace = torch.ones(16 * 32 * 8, dtype=torch.uint8)
+        assert not sh.workspace_clean
+    del seen[:]
+    for call in reads * 2:
+        call(sh)
+    assert seen == [0] * 2 * len(reads)
+    if cls is pk.Shard:
+        pk.adamw_commit(sh, 1)
+        assert seen[-1] == 1 and sh.workspace_clean
