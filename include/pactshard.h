@@ -252,6 +252,8 @@ typedef struct pact_workspace_state {
  * workspace holds two sets of partial sums: successive calls alternate, and
  * each also clears the other's set, so a workspace that was written to behind
  * the state's back costs one wrong result (or one left as it was) and no more.
+ * A call that is being captured into a graph clears the workspace whatever the
+ * state says, and leaves the state alone: its replays may find anything there.
  * A state belongs to one workspace and, as the workspace, to one call at a
  * time.  flags: 0 or PACT_COMMIT_ZERO_GRAD. */
 int pact_adamw_commit_ws(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags,

@@ -400,15 +400,24 @@ Tiling tiling_of(pact::Mode mode, const View& s, size_t nwork) {
     return t;
 }
 
-// What the caller says about the workspace: clean = every node is zero (the
-// tile kernels leave them so), and the clearing launch is skipped; odd = the
+// Whether calls on the stream are being recorded instead of run (the legacy
+// null stream's cannot be).
+bool is_capturing(void* stream) {
+    if (stream == nullptr) return false;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(static_cast<hipStream_t>(stream), &status);
+    return e != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
+// What a call may take for granted of the workspace: clean = every node is zero
+// (the tile kernels leave them so), and the clearing launch is skipped; odd = the
 // call uses the second set of nodes.
 struct Workspace {
     bool clean = false;
     bool odd = false;
 };
 
-int run(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, uint64_t nslots, Workspace ws) {
+int enqueue(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, uint64_t nslots, Workspace ws) {
     hipStream_t stream = static_cast<hipStream_t>(s.stream);
     const uint32_t nres = (uint32_t)result_slots(s);
     const bool per_segment = s.segs != nullptr;
@@ -490,6 +499,30 @@ int run(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, ui
     return PACT_OK;
 }
 
+// The call in the state `ws` (null: nothing is known of the workspace).  One that
+// is being captured says nothing about the workspace when it is replayed, so it
+// clears it, and it has not run, so it leaves the state alone.  (A replay that
+// takes the workspace to be clear would use the same nodes every time, and once
+// these were not clear no replay would find its last arrival again.)
+int run(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out, uint64_t nslots,
+        pact_workspace_state* ws) {
+    if (ws == nullptr || s.workspace == nullptr || is_capturing(s.stream)) {
+        const int rc = enqueue(mode, s, work, out, nslots, {});
+        if (rc == PACT_EHIP && ws != nullptr) ws->clear = 0;
+        return rc;
+    }
+    const int rc =
+        enqueue(mode, s, work, out, nslots, {ws->clear != 0 && ws->stream == s.stream, (ws->odd & 1u) != 0});
+    if (rc == PACT_OK) {
+        ws->stream = s.stream;
+        ws->clear = 1;
+        ws->odd ^= 1u;
+    } else if (rc == PACT_EHIP) {
+        ws->clear = 0;
+    }
+    return rc;
+}
+
 // ---------------------------------------------------------------------------
 // Static scratch of pact_adamw_commit_static: the digest nodes of up to
 // PACT_STATIC_MAX_SEGMENTS result slots in device memory the library holds
@@ -541,8 +574,8 @@ int static_scratch_ptr(void* stream, void** out) {
 // A commit mode: check step and hyperparameters, validate, enqueue.  With
 // static_scratch the nodes are the library's static array (the caller's
 // workspace must be absent).
-int commit(pact::Mode mode, View s, uint64_t step, const pact_hyper* hyper, const Uses& use, Workspace ws,
-           bool static_scratch = false) {
+int commit(pact::Mode mode, View s, uint64_t step, const pact_hyper* hyper, const Uses& use,
+           pact_workspace_state* ws, bool static_scratch = false) {
     if (step == 0) return PACT_EINVAL;
     if (s.segs == nullptr && (hyper == nullptr || !hyper_ok(*hyper))) return PACT_EINVAL;
     uint64_t nslots = 0;
@@ -558,46 +591,19 @@ int commit(pact::Mode mode, View s, uint64_t step, const pact_hyper* hyper, cons
         if (rc != PACT_OK) return rc;
         s.workspace = words;
         s.workspace_bytes = kStaticScratchBytes;
-        ws = Workspace{};  // shared by every call on the GPU: always cleared first
+        ws = nullptr;  // shared by every call on the GPU: always cleared first
     }
     const SegSource work{&s, hyper, step, true};
     return run(mode, s, work, s.digest, nslots, ws);
 }
 
 // A mode that only reads the shard: validate, enqueue.
-int measure(pact::Mode mode, const View& s, const Uses& use, uint64_t* out, Workspace ws) {
+int measure(pact::Mode mode, const View& s, const Uses& use, uint64_t* out, pact_workspace_state* ws) {
     uint64_t nslots = 0;
     int rc = validate(s, use, out, &nslots);
     if (rc != PACT_OK) return rc;
     const SegSource work{&s, nullptr, 0, false};
     return run(mode, s, work, out, nslots, ws);
-}
-
-// What a call may take for granted of the workspace in the state `ws`.
-template <typename S>
-Workspace workspace_of(const S* s, const pact_workspace_state* ws) {
-    if (ws == nullptr) return {};
-    return {ws->clear != 0 && ws->stream == s->stream, (ws->odd & 1u) != 0};
-}
-
-// The state after a call that returned rc.  A call that was captured has not
-// run: it proves nothing about a workspace that was not known to be clear.
-template <typename S>
-int note_workspace(const S* s, pact_workspace_state* ws, int rc) {
-    if (ws == nullptr || s == nullptr) return rc;
-    if (rc == PACT_EHIP) {
-        ws->clear = 0;
-    } else if (rc == PACT_OK && s->workspace != nullptr) {
-        if (ws->clear == 0 && s->stream != nullptr) {
-            hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-            const hipError_t e = hipStreamIsCapturing(static_cast<hipStream_t>(s->stream), &status);
-            if (e != hipSuccess || status != hipStreamCaptureStatusNone) return rc;
-        }
-        ws->stream = s->stream;
-        ws->clear = 1;
-        ws->odd ^= 1u;
-    }
-    return rc;
 }
 
 constexpr Uses kUsesAll = {{true, true, true, true, true}};
@@ -636,8 +642,8 @@ int64_t pact_workspace_bytes_bf16(const pact_shard_bf16* s) {
 
 int pact_adamw_commit_ex(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags) {
     if (s == nullptr || (flags & ~(PACT_COMMIT_ZERO_GRAD | PACT_COMMIT_WORKSPACE_CLEAN)) != 0) return PACT_EINVAL;
-    return commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll,
-                  {(flags & PACT_COMMIT_WORKSPACE_CLEAN) != 0, false});
+    pact_workspace_state known = {s->stream, (flags & PACT_COMMIT_WORKSPACE_CLEAN) != 0, 0};
+    return commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll, &known);
 }
 
 int pact_adamw_commit(const pact_shard* s, uint64_t step, const pact_hyper* hyper) {
@@ -647,35 +653,31 @@ int pact_adamw_commit(const pact_shard* s, uint64_t step, const pact_hyper* hype
 int pact_adamw_commit_ws(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags,
                          pact_workspace_state* ws) {
     if (s == nullptr || (flags & ~PACT_COMMIT_ZERO_GRAD) != 0) return PACT_EINVAL;
-    return note_workspace(s, ws,
-                          commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll, workspace_of(s, ws)));
+    return commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll, ws);
 }
 
 int pact_adamw_commit_static(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags) {
     if (s == nullptr || (flags & ~PACT_COMMIT_ZERO_GRAD) != 0) return PACT_EINVAL;
-    return commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll, {}, true);
+    return commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll, nullptr, true);
 }
 
 int pact_grad_guard_ws(const pact_shard* s, uint64_t* dev_out, pact_workspace_state* ws) {
     if (s == nullptr) return PACT_EINVAL;
-    return note_workspace(s, ws,
-                          measure(pact::Mode::GradGuard, view_of(s), kUsesGrad, dev_out, workspace_of(s, ws)));
+    return measure(pact::Mode::GradGuard, view_of(s), kUsesGrad, dev_out, ws);
 }
 
 int pact_grad_guard(const pact_shard* s, uint64_t* dev_out) { return pact_grad_guard_ws(s, dev_out, nullptr); }
 
 int pact_shard_digest_ws(const pact_shard* s, pact_workspace_state* ws) {
     if (s == nullptr) return PACT_EINVAL;
-    return note_workspace(
-        s, ws, measure(pact::Mode::StateDigest, view_of(s), kUsesState, s->digest_dev, workspace_of(s, ws)));
+    return measure(pact::Mode::StateDigest, view_of(s), kUsesState, s->digest_dev, ws);
 }
 
 int pact_shard_digest(const pact_shard* s) { return pact_shard_digest_ws(s, nullptr); }
 
 int pact_bf16_digest_ws(const pact_shard* s, uint64_t* dev_out, pact_workspace_state* ws) {
     if (s == nullptr) return PACT_EINVAL;
-    return note_workspace(s, ws,
-                          measure(pact::Mode::Bf16Digest, view_of(s), kUsesCopy, dev_out, workspace_of(s, ws)));
+    return measure(pact::Mode::Bf16Digest, view_of(s), kUsesCopy, dev_out, ws);
 }
 
 int pact_bf16_digest(const pact_shard* s, uint64_t* dev_out) { return pact_bf16_digest_ws(s, dev_out, nullptr); }
@@ -683,8 +685,7 @@ int pact_bf16_digest(const pact_shard* s, uint64_t* dev_out) { return pact_bf16_
 int pact_adamw_commit_bf16_ws(const pact_shard_bf16* s, uint64_t step, const pact_hyper* hyper,
                               pact_workspace_state* ws) {
     if (s == nullptr) return PACT_EINVAL;
-    return note_workspace(
-        s, ws, commit(pact::Mode::CommitBf16State, view_of(s), step, hyper, kUsesAllBf16, workspace_of(s, ws)));
+    return commit(pact::Mode::CommitBf16State, view_of(s), step, hyper, kUsesAllBf16, ws);
 }
 
 int pact_adamw_commit_bf16(const pact_shard_bf16* s, uint64_t step, const pact_hyper* hyper) {
@@ -693,8 +694,7 @@ int pact_adamw_commit_bf16(const pact_shard_bf16* s, uint64_t step, const pact_h
 
 int pact_shard_digest_bf16_ws(const pact_shard_bf16* s, pact_workspace_state* ws) {
     if (s == nullptr) return PACT_EINVAL;
-    return note_workspace(
-        s, ws, measure(pact::Mode::DigestBf16State, view_of(s), kUsesState, s->digest_dev, workspace_of(s, ws)));
+    return measure(pact::Mode::DigestBf16State, view_of(s), kUsesState, s->digest_dev, ws);
 }
 
 int pact_shard_digest_bf16(const pact_shard_bf16* s) { return pact_shard_digest_bf16_ws(s, nullptr); }

@@ -186,3 +186,40 @@ def test_reads_after_the_caller_wrote_to_the_workspace(n, how):
         assert pk.to_u64(pk.adamw_commit_bf16(sh, step, pk.Hyper(**H))) == [want]
         dirty(sh, kept)
         assert pk.to_u64(pk.shard_digest_bf16(sh)) == [want]
+
+
+@pytest.mark.parametrize("call", ["digest", "commit"])
+def test_replays_after_a_workspace_that_was_not_clear(call):
+    """A call captured on the very stream the state vouches for: replays are right
+    whatever the workspace holds by then."""
+    import torch
+
+    pk = _pk()
+    n = 70 * T + 9
+    p, g, m, v = _state(n, 7)
+    sh = make_shard(p, g, m, v, 31)
+    b = np.zeros(n, np.uint16)
+
+    def go():
+        return pk.shard_digest(sh) if call == "digest" else pk.adamw_commit(sh, 4, pk.Hyper(**H))
+
+    def want():
+        if call == "digest":
+            return [oracle.state_digest(p, m, v, 31)]
+        return [oracle.commit_and_digest(p, g, m, v, b, o_hyper(H), 4, 31)]
+
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        assert pk.to_u64(go()) == want()
+        with torch.cuda.graph(graph, stream=side):
+            go()
+        for k in range(4):
+            sh.digest.fill_(-1)
+            if k != 1:
+                sh.workspace.fill_(0x5A)
+            graph.replay()
+            assert pk.to_u64(sh.digest) == want(), k
+        if call == "digest":
+            assert pk.to_u64(go()) == want()
