@@ -135,8 +135,8 @@ int64_t pact_digest_slots(const pact_shard* s);
  * with no launch behind the tiles.  The caller allocates it (8-byte
  * aligned, disjoint from every other buffer) and may reuse it for any later
  * call on the same stream.  Its contents on entry do not matter (the call
- * clears the part it uses first, unless told with PACT_COMMIT_WORKSPACE_CLEAN
- * that it is clear already), and every call that returns PACT_OK leaves that
+ * clears the part it uses first, unless a pact_workspace_state says that it is
+ * clear already), and every call that returns PACT_OK leaves that
  * part zero again once the stream has run it.  workspace == NULL is valid:
  * the call is then correct but slower.  A non-NULL workspace with
  * workspace_bytes below this figure is PACT_EINVAL.  Negative error code if s
@@ -151,7 +151,7 @@ int pact_adamw_commit(const pact_shard* s, uint64_t step, const pact_hyper* hype
 
 /* Options of pact_adamw_commit_ex. */
 #define PACT_COMMIT_ZERO_GRAD 1u       /* the same pass writes +0.0 into every committed grad element */
-#define PACT_COMMIT_WORKSPACE_CLEAN 2u /* the workspace is already clear: skip clearing it */
+#define PACT_COMMIT_WORKSPACE_CLEAN 2u /* the workspace is already clear */
 
 /* The commit with options; flags = 0 is exactly pact_adamw_commit.
  * PACT_COMMIT_ZERO_GRAD: after reading g, the same pass writes +0.0 into
@@ -159,11 +159,11 @@ int pact_adamw_commit(const pact_shard* s, uint64_t step, const pact_hyper* hype
  * so that one call leaves the shard at the boundary the paper admits for
  * in-memory recovery: update committed and flat gradients zeroed (Sec. I;
  * Sec. III-C, phase 2).  `grad` must then be writable device memory.
- * PACT_COMMIT_WORKSPACE_CLEAN: the caller vouches that the workspace is clear
+ * PACT_COMMIT_WORKSPACE_CLEAN: the caller knows that the workspace is clear
  * (zero-filled before its first use, and touched since then only by calls on
- * this stream that returned PACT_OK), so the call skips the launch that
- * clears it; a workspace in any other state gives a wrong digest (or leaves
- * the digest slots as they were).  Without a workspace the flag has no effect.
+ * this stream that returned PACT_OK).  The flag is accepted and has no effect:
+ * the call clears the workspace all the same.  pact_adamw_commit_ws is the call
+ * that can leave the clearing out.
  * Unknown flag bits are PACT_EINVAL. */
 int pact_adamw_commit_ex(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags);
 

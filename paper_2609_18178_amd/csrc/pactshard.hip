@@ -642,8 +642,9 @@ int64_t pact_workspace_bytes_bf16(const pact_shard_bf16* s) {
 
 int pact_adamw_commit_ex(const pact_shard* s, uint64_t step, const pact_hyper* hyper, uint32_t flags) {
     if (s == nullptr || (flags & ~(PACT_COMMIT_ZERO_GRAD | PACT_COMMIT_WORKSPACE_CLEAN)) != 0) return PACT_EINVAL;
-    pact_workspace_state known = {s->stream, (flags & PACT_COMMIT_WORKSPACE_CLEAN) != 0, 0};
-    return commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll, &known);
+    // PACT_COMMIT_WORKSPACE_CLEAN without a state to alternate the workspace's sets
+    // would never find out of one that was not clear: the call clears all the same.
+    return commit(commit_mode(flags), view_of(s), step, hyper, kUsesAll, nullptr);
 }
 
 int pact_adamw_commit(const pact_shard* s, uint64_t step, const pact_hyper* hyper) {

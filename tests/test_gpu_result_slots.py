@@ -2,6 +2,8 @@
 sides of the split into lanes, one and many segments (empty ones among them),
 the call that follows a workspace written to behind the state's back, and calls
 that change streams.  Digests are whole numbers and compare exactly."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -223,3 +225,25 @@ def test_replays_after_a_workspace_that_was_not_clear(call):
             assert pk.to_u64(sh.digest) == want(), k
         if call == "digest":
             assert pk.to_u64(go()) == want()
+
+
+def test_commits_told_that_the_workspace_is_clear():
+    """PACT_COMMIT_WORKSPACE_CLEAN in call after call at one step: a workspace that
+    was not clear costs no call behind the next one."""
+    import torch
+
+    pk = _pk()
+    n = 70 * T + 9
+    p, g, m, v = _state(n, 8)
+    sh = make_shard(p, g, m, v, 31)
+    b = np.zeros(n, np.uint16)
+    for _ in range(2):
+        sh.workspace.fill_(0x5A)
+        for k in range(3):
+            want = oracle.commit_and_digest(p, g, m, v, b, o_hyper(H), 4, 31)
+            rc = pk._lib().pact_adamw_commit_ex(ctypes.byref(sh._c()), 4, ctypes.byref(pk.Hyper(**H)._c()),
+                                                pk.PACT_COMMIT_WORKSPACE_CLEAN)
+            assert rc == pk.PACT_OK
+            got = pk.to_u64(sh.digest)
+            assert k == 0 or got == [want], k
+    torch.cuda.synchronize()
