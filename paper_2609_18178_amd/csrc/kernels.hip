@@ -683,11 +683,11 @@ struct Words16<4> {
 // one element, element-wise path (ragged tails, misaligned segments)
 // ---------------------------------------------------------------------------
 template <Mode M>
-constexpr bool kCommits = (M == Mode::Commit || M == Mode::CommitZeroGrad);
+constexpr bool kCommits = binary32_commit(M);
 
-// Modes whose tiles may have several passes.
-template <Mode M>
-constexpr bool kManyPasses = (M == Mode::Bf16Digest || M == Mode::DigestBf16State);
+// Kernels whose tiles may have several passes.
+template <Mode M, Form F>
+constexpr bool kManyPasses = F == Form::Usual && (M == Mode::Bf16Digest || M == Mode::DigestBf16State);
 
 // Modes whose digest words have 16 bits (the short IndexLo16 form applies).
 template <Mode M>
@@ -976,9 +976,9 @@ __device__ __forceinline__ uint32_t dealt_tile(uint32_t tiles, uint32_t run) {
     return tiles - first >= group ? first + r % kXcds * run + r / kXcds : blockIdx.x;
 }
 
-template <Mode M, bool Small>
+template <Mode M, Form F>
 __device__ __forceinline__ uint32_t tile_of_block(uint32_t tiles) {
-    constexpr Runs kRuns = runs_of(M, Small);
+    constexpr Runs kRuns = runs_of(M, F);
     if (tiles >= kRuns.long_from) return dealt_tile(tiles, kRuns.long_run);
     if (tiles >= kRuns.from) return dealt_tile(tiles, kRuns.run);
     return blockIdx.x;
@@ -999,12 +999,12 @@ __device__ __forceinline__ void load_now(const ArraysBf16& a) {
     asm volatile("" ::"s"(a.p), "s"(a.g), "s"(a.m), "s"(a.v), "s"(a.goff));
 }
 
-template <Mode M, bool Small, typename A>
+template <Mode M, Form F, typename A>
 __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t* lds) {
-    constexpr Shape kShape = shape_of(M, Small);
+    constexpr Shape kShape = shape_of(M, F);
     constexpr int kVecs = kShape.vec, kRows = kShape.rows;
     constexpr uint32_t kPass = kShape.elems();
-    const uint32_t passes = kManyPasses<M> && !Small ? bt.passes : 1;
+    const uint32_t passes = kManyPasses<M, F> ? bt.passes : 1;
     const uint32_t tile_elems = kPass * passes;
     // The tile's segment.  Segment 0's line is loaded together with the number of
     // segments, so what a flat shard needs is there after one wait; else the segment
@@ -1017,7 +1017,7 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
     load_now(a);
     asm volatile("" : "+s"(nseg), "+s"(tiles));
     load_now(sg);
-    const uint32_t tile = tile_of_block<M, Small>(tiles);
+    const uint32_t tile = tile_of_block<M, F>(tiles);
     if (nseg > 1) {
 #pragma unroll
         for (int k = 1; k < kSegsPerLaunch; ++k) {
@@ -1050,7 +1050,7 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
         const uint64_t left = e0 < seg_end ? seg_end - e0 : 0;
         const uint32_t whole = left < tile_elems ? (uint32_t)left / kPass : passes;  // the tile's whole passes
         auto one_pass = [&](uint64_t at) { acc += do_pass<M, kVecs, kRows>(a, at, sc); };
-        if constexpr (kManyPasses<M> && !Small) {
+        if constexpr (kManyPasses<M, F>) {
 #pragma unroll 1
             for (uint32_t pass = 0; pass < whole; ++pass) one_pass(uniform(e0 + pass * kPass));
         } else if (whole != 0) {
@@ -1123,23 +1123,23 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
 // digest to 66 VGPRs and seven waves).  The BF16-state commit takes 64 VGPRs in
 // either case, scheduled for eight waves in its small shape (6M elements 18.6 us
 // against 19.6) and for six in the large one (453M 1115 us against 1128).
-template <Mode M, bool Small>
+template <Mode M, Form F>
 constexpr unsigned kMinWavesPerSimd = (M == Mode::StateDigest || M == Mode::DigestBf16State) ? 8u
-                                      : (M == Mode::CommitBf16State)                         ? (Small ? 8u : 6u)
+                                      : (M == Mode::CommitBf16State)                         ? (F == Form::Small ? 8u : 6u)
                                                                                              : 1u;
 
-template <Mode M, bool Small>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWavesPerSimd<M, Small>)))
+template <Mode M, Form F>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWavesPerSimd<M, F>)))
 void tile_kernel(Arrays a, Batch bt) {
     __shared__ uint64_t lds[kBlock / 64];
-    tile_body<M, Small>(a, bt, lds);
+    tile_body<M, F>(a, bt, lds);
 }
 
-template <Mode M, bool Small>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWavesPerSimd<M, Small>)))
+template <Mode M, Form F>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMinWavesPerSimd<M, F>)))
 void tile_kernel_bf16(ArraysBf16 a, Batch bt) {
     __shared__ uint64_t lds[kBlock / 64];
-    tile_body<M, Small>(a, bt, lds);
+    tile_body<M, F>(a, bt, lds);
 }
 
 // Clears what the tile kernels hand their shares in to: every node of both
@@ -1269,48 +1269,51 @@ namespace {
 //   4 KB tiles, three per CU               2721 (4.99)
 // Five rather than four keeps the arena's rate.  The 16-bit state's commit and
 // the digests were slower with less in flight.
-template <Mode M>
-constexpr uint32_t kReserveLds = kCommits<M> ? 30u << 10 : 0u;
+template <Mode M, Form F>
+constexpr uint32_t kReserveLds = kCommits<M> && F == Form::Usual ? 30u << 10 : 0u;
 
 template <Mode M>
-void launch_tiles(bool small, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream) {
+void launch_tiles(Form form, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream) {
+    auto launch = [&](auto kernel, uint32_t lds) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), lds, stream, a, b);
+    };
     if constexpr (small_up_to(M) != 0) {
-        if (small) {
-            hipLaunchKernelGGL((tile_kernel<M, true>), dim3(grid), dim3(kBlock), 0, stream, a, b);
-            return;
-        }
+        if (form == Form::Small) return launch(tile_kernel<M, Form::Small>, 0);
     }
-    hipLaunchKernelGGL((tile_kernel<M, false>), dim3(grid), dim3(kBlock), kReserveLds<M>, stream, a, b);
+    if constexpr (kCommits<M>) {
+        if (form == Form::Long) return launch(tile_kernel<M, Form::Long>, kReserveLds<M, Form::Long>);
+    }
+    launch(tile_kernel<M, Form::Usual>, kReserveLds<M, Form::Usual>);
 }
 
 template <Mode M>
-void launch_tiles(bool small, const ArraysBf16& a, const Batch& b, uint32_t grid, hipStream_t stream) {
-    if (small) {
-        hipLaunchKernelGGL((tile_kernel_bf16<M, true>), dim3(grid), dim3(kBlock), 0, stream, a, b);
+void launch_tiles(Form form, const ArraysBf16& a, const Batch& b, uint32_t grid, hipStream_t stream) {
+    if (form == Form::Small) {
+        hipLaunchKernelGGL((tile_kernel_bf16<M, Form::Small>), dim3(grid), dim3(kBlock), 0, stream, a, b);
     } else {
-        hipLaunchKernelGGL((tile_kernel_bf16<M, false>), dim3(grid), dim3(kBlock), 0, stream, a, b);
+        hipLaunchKernelGGL((tile_kernel_bf16<M, Form::Usual>), dim3(grid), dim3(kBlock), 0, stream, a, b);
     }
 }
 
 }  // namespace
 
-hipError_t launch_batch(Mode mode, bool small, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream) {
+hipError_t launch_batch(Mode mode, Form form, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream) {
     switch (mode) {
-        case Mode::Commit: launch_tiles<Mode::Commit>(small, a, b, grid, stream); break;
-        case Mode::StateDigest: launch_tiles<Mode::StateDigest>(small, a, b, grid, stream); break;
-        case Mode::Bf16Digest: launch_tiles<Mode::Bf16Digest>(small, a, b, grid, stream); break;
-        case Mode::CommitZeroGrad: launch_tiles<Mode::CommitZeroGrad>(small, a, b, grid, stream); break;
-        case Mode::GradGuard: launch_tiles<Mode::GradGuard>(small, a, b, grid, stream); break;
+        case Mode::Commit: launch_tiles<Mode::Commit>(form, a, b, grid, stream); break;
+        case Mode::StateDigest: launch_tiles<Mode::StateDigest>(form, a, b, grid, stream); break;
+        case Mode::Bf16Digest: launch_tiles<Mode::Bf16Digest>(form, a, b, grid, stream); break;
+        case Mode::CommitZeroGrad: launch_tiles<Mode::CommitZeroGrad>(form, a, b, grid, stream); break;
+        case Mode::GradGuard: launch_tiles<Mode::GradGuard>(form, a, b, grid, stream); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_batch_bf16(Mode mode, bool small, const ArraysBf16& a, const Batch& b, uint32_t grid,
+hipError_t launch_batch_bf16(Mode mode, Form form, const ArraysBf16& a, const Batch& b, uint32_t grid,
                              hipStream_t stream) {
     switch (mode) {
-        case Mode::CommitBf16State: launch_tiles<Mode::CommitBf16State>(small, a, b, grid, stream); break;
-        case Mode::DigestBf16State: launch_tiles<Mode::DigestBf16State>(small, a, b, grid, stream); break;
+        case Mode::CommitBf16State: launch_tiles<Mode::CommitBf16State>(form, a, b, grid, stream); break;
+        case Mode::DigestBf16State: launch_tiles<Mode::DigestBf16State>(form, a, b, grid, stream); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -113,15 +113,20 @@ struct Shape {
     constexpr uint32_t elems() const { return (uint32_t)(kBlock * vec * rows); }
 };
 
+// The instantiations of a mode's tile kernel: the usual one, one for shards that
+// would leave most of the GPU idle, and one with longer tiles.
+enum class Form : int { Usual, Small, Long };
+
 // The commits of binary32 state move one row of 4 KB per array (the comment at
-// kReserveLds in kernels.hip says why); the others' kernels, bound by reading or by
-// VALU issue, have more loads in flight per thread, and a second shape of one
-// short row for shards that would leave most of the GPU idle (small).
-constexpr Shape shape_of(Mode m, bool small) {
+// kReserveLds in kernels.hip says why), or four (Long); the others' kernels, bound by
+// reading or by VALU issue, have more loads in flight per thread, and a second shape of
+// one short row for shards that would leave most of the GPU idle (Small).
+constexpr Shape shape_of(Mode m, Form f) {
+    const bool small = f == Form::Small;
     switch (m) {
         case Mode::Commit:
         case Mode::CommitZeroGrad:
-            return {4, 1};
+            return f == Form::Long ? Shape{4, 4} : Shape{4, 1};
         case Mode::GradGuard:
             return {4, 4};
         case Mode::StateDigest:
@@ -133,6 +138,8 @@ constexpr Shape shape_of(Mode m, bool small) {
     }
     return {4, 1};
 }
+
+constexpr bool binary32_commit(Mode m) { return m == Mode::Commit || m == Mode::CommitZeroGrad; }
 
 // Elements up to which the small shape is the faster one (0: there is none).
 // us per call, small / large shape, at 0.1M, 1M, 4M and 16M elements:
@@ -151,6 +158,16 @@ constexpr uint64_t small_up_to(Mode m) {
     }
 }
 
+// The form of a call over `elems` elements.  Without a workspace each tile adds its
+// share to the one result word, 12 ns per tile whatever else the call does, so its tiles
+// are the longest there are.  us per call of 1M and 453M elements without a workspace, in
+// tiles of 1024 and of 4096 elements: commit 17.1 / 11.2 and 5504 / 2420; of 1M and 3M,
+// state digest 16.1 / 9.2 and 40.0 / 15.0; BF16 commit of 16M 196 / 64.
+constexpr Form form_of(Mode m, uint64_t elems, bool workspace) {
+    if (!workspace) return binary32_commit(m) ? Form::Long : Form::Usual;
+    return elems <= small_up_to(m) ? Form::Small : Form::Usual;
+}
+
 // Consecutive tiles per XCD: a workgroup's XCD is its number modulo 8, so tiles
 // are dealt in groups of 8 * run, of which each XCD takes `run` neighbours.
 // Grids below `from` tiles keep their order.
@@ -159,8 +176,9 @@ struct Runs {
     uint32_t long_run, long_from;
 };
 constexpr uint32_t kXcds = 8;
-constexpr Runs runs_of(Mode m, bool small) {
+constexpr Runs runs_of(Mode m, Form f) {
     constexpr uint32_t kNever = ~0u;
+    if (f != Form::Usual) return {1, kNever, 1, kNever};
     switch (m) {
         case Mode::Commit:
         case Mode::CommitZeroGrad:
@@ -174,7 +192,7 @@ constexpr Runs runs_of(Mode m, bool small) {
             // 16 tiles against 1: guard of 453M elements 288 -> 266 us, BF16
             // digest 728 -> 720, BF16 commit 1237 -> 1225; below 8M elements
             // up to 7% slower.
-            return small ? Runs{1, kNever, 1, kNever} : Runs{16, 2048, 16, kNever};
+            return {16, 2048, 16, kNever};
     }
 }
 
@@ -182,12 +200,12 @@ constexpr Runs runs_of(Mode m, bool small) {
 // nodes of nres result slots when `words` is given, else the nslots digest slots.
 hipError_t launch_clear(uint64_t* digest, uint64_t* words, uint32_t nres, uint32_t nslots, hipStream_t stream);
 
-// Enqueue one batch in the given mode, in tiles of shape_of(mode, small): one
+// Enqueue one batch in the given mode, in tiles of shape_of(mode, form): one
 // workgroup per tile, so `grid` is the batch's tile count.
-hipError_t launch_batch(Mode mode, bool small, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream);
+hipError_t launch_batch(Mode mode, Form form, const Arrays& a, const Batch& b, uint32_t grid, hipStream_t stream);
 
 // Enqueue one batch of a BF16-state mode (CommitBf16State, DigestBf16State).
-hipError_t launch_batch_bf16(Mode mode, bool small, const ArraysBf16& a, const Batch& b, uint32_t grid,
+hipError_t launch_batch_bf16(Mode mode, Form form, const ArraysBf16& a, const Batch& b, uint32_t grid,
                              hipStream_t stream);
 
 // Enqueue digest[nres] = sum of digest[0..nres).

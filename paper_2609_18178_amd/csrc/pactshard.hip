@@ -13,9 +13,10 @@
 // What the kernels and the batching below rely on.
 static_assert(pact::kBlock % 64 == 0 && pact::kBlock <= 1024, "whole waves of 64, one block");
 static_assert(pact::kVec == 4, "the binary32 vector path moves 16-byte vectors of four elements");
-static_assert(pact::shape_of(pact::Mode::CommitBf16State, false).elems() == pact::kTile &&
-                  pact::shape_of(pact::Mode::StateDigest, false).elems() == pact::kTile &&
-                  pact::kTile % pact::shape_of(pact::Mode::Commit, false).elems() == 0,
+static_assert(pact::shape_of(pact::Mode::CommitBf16State, pact::Form::Usual).elems() == pact::kTile &&
+                  pact::shape_of(pact::Mode::StateDigest, pact::Form::Usual).elems() == pact::kTile &&
+                  pact::shape_of(pact::Mode::Commit, pact::Form::Long).elems() == pact::kTile &&
+                  pact::kTile % pact::shape_of(pact::Mode::Commit, pact::Form::Usual).elems() == 0,
               "tiles grow to kTile, the unit of the grid limit");
 static_assert((pact::kLanes & (pact::kLanes - 1)) == 0, "lane = tile & (kLanes - 1)");
 static_assert(pact::kLanes >= 2, "the total's node sits beside lane 1's");
@@ -361,8 +362,8 @@ uint64_t tiles_of(uint64_t count, uint32_t align, uint64_t tile) {
 
 // How a call cuts its segments into tiles.
 struct Tiling {
-    bool small;       // the mode's small shape
-    uint32_t passes;  // of that shape in a tile
+    pact::Form form;
+    uint32_t passes;  // of the form's shape in a tile
     uint64_t elems;   // of a tile
     uint64_t tiles;   // of the call
     bool fits;        // every segment's tiles fit one launch
@@ -375,10 +376,10 @@ Tiling tiling_of(pact::Mode mode, const View& s, size_t nwork) {
         for (size_t k = 0; k < nwork; ++k) elems += s.segs[k].length;
     }
     Tiling t;
-    t.small = elems <= pact::small_up_to(mode);
-    const uint64_t pass = pact::shape_of(mode, t.small).elems();
+    t.form = pact::form_of(mode, elems, s.workspace != nullptr);
+    const uint64_t pass = pact::shape_of(mode, t.form).elems();
     t.passes = 1;
-    if (!t.small && (mode == pact::Mode::Bf16Digest || mode == pact::Mode::DigestBf16State)) {
+    if (t.form == pact::Form::Usual && (mode == pact::Mode::Bf16Digest || mode == pact::Mode::DigestBf16State)) {
         // The 16-bit digests spend a few percent of a short tile on its start
         // and end: two passes once 8192 tiles are left, four likewise (bf16
         // digest of 76M and 453M elements 48.8 -> 47.0 and 263 -> 242 us, BF16
@@ -486,8 +487,8 @@ int enqueue(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out
         b.nseg = (uint32_t)cnt;
         b.tiles = (uint32_t)tiles;
         std::fill(b.tile_begin + cnt, b.tile_begin + pact::kSegsPerLaunch, ~0u);
-        e = is_bf16_state(mode) ? pact::launch_batch_bf16(mode, t.small, ab, b, (uint32_t)tiles, stream)
-                                : pact::launch_batch(mode, t.small, a, b, (uint32_t)tiles, stream);
+        e = is_bf16_state(mode) ? pact::launch_batch_bf16(mode, t.form, ab, b, (uint32_t)tiles, stream)
+                                : pact::launch_batch(mode, t.form, a, b, (uint32_t)tiles, stream);
         if (e != hipSuccess) return fail_hip(e);
         first += cnt;
         tile0 += tiles;

@@ -23,10 +23,11 @@ def _pk():
     return pk
 
 
-def _table(shift):
-    """Segments of all LENGTHS; segment k starts `shift` + k elements (mod 8)
-    behind an aligned element, with a gap of at least one before it."""
-    segs, off = [], 0
+def _table(shift, lead=0):
+    """Segments of all LENGTHS, behind one of `lead` elements if any; segment k starts
+    `shift` + k elements (mod 8) behind an aligned element, with a gap of at least one
+    before it."""
+    segs, off = [(0, lead, 0)] if lead else [], lead
     for k, ln in enumerate(LENGTHS):
         off = (off + 8) // 8 * 8 + (shift + k) % 8
         segs.append((off, ln, 0))
@@ -62,16 +63,13 @@ def _margins_untouched(whole, bases, n):
 BASES = {"together": (0, 0, 0, 0, 0), "shifted": (3, 3, 3, 3, 3), "grad apart": (0, 1, 0, 0, 0), "copy apart": (0, 0, 0, 0, 2)}
 
 
-@pytest.mark.parametrize("bases", list(BASES))
-@pytest.mark.parametrize("shift", [0, 1, 6])
-@pytest.mark.parametrize("goff", [5, (1 << 32) - 9000])
-def test_binary32_segments(bases, shift, goff):
+def _check_binary32(bases, shift, goff, lead=0, use_workspace=True):
     import torch
 
     pk = _pk()
-    segs, n = _table(shift)
+    segs, n = _table(shift, lead)
     (p, g, m, v), dev, whole = _arrays(n, BASES[bases], torch.float32)
-    sh = pk.Shard(*dev, goff, segments=segs, hypers=[g_hyper(H)])
+    sh = pk.Shard(*dev, goff, segments=segs, hypers=[g_hyper(H)], use_workspace=use_workspace)
     per, total = oracle.segment_digests(p, m, v, segs, goff)
     assert pk.to_u64(pk.shard_digest(sh)) == per + [total]
     counts = [int(np.count_nonzero(g[o:o + ln].view(np.uint32))) for o, ln, _ in segs]
@@ -92,16 +90,13 @@ def test_binary32_segments(bases, shift, goff):
     _margins_untouched(whole, BASES[bases], n)
 
 
-@pytest.mark.parametrize("bases", ["together", "shifted", "grad apart"])
-@pytest.mark.parametrize("shift", [0, 3, 7])
-@pytest.mark.parametrize("goff", [5, (1 << 16) - 300])
-def test_bf16_state_segments(bases, shift, goff):
+def _check_bf16_state(bases, shift, goff, lead=0, use_workspace=True):
     import torch
 
     pk = _pk()
-    segs, n = _table(shift)
+    segs, n = _table(shift, lead)
     (p, g, m, v), dev, whole = _arrays(n, BASES[bases], torch.int16)
-    sh = pk.ShardBf16(*dev[:4], goff, segments=segs, hypers=[g_hyper(H)])
+    sh = pk.ShardBf16(*dev[:4], goff, segments=segs, hypers=[g_hyper(H)], use_workspace=use_workspace)
     want = [oracle.state_digest_bf16(p[o:o + ln], m[o:o + ln], v[o:o + ln], goff + o) for o, ln, _ in segs]
     assert pk.to_u64(pk.shard_digest_bf16(sh))[:-1] == want
     want = [oracle.commit_and_digest_bf16(p[o:o + ln], g[o:o + ln], m[o:o + ln], v[o:o + ln], o_hyper(H), 6, goff + o)
@@ -110,3 +105,27 @@ def test_bf16_state_segments(bases, shift, goff):
     for name, ref in (("param", p), ("exp_avg", m), ("exp_avg_sq", v)):
         assert_bitwise(name, host(getattr(sh, name)).view(np.uint16), ref)
     _margins_untouched(whole, BASES[bases], n)
+
+
+@pytest.mark.parametrize("bases", list(BASES))
+@pytest.mark.parametrize("shift", [0, 1, 6])
+@pytest.mark.parametrize("goff", [5, (1 << 32) - 9000])
+def test_binary32_segments(bases, shift, goff):
+    _check_binary32(bases, shift, goff)
+
+
+@pytest.mark.parametrize("bases", ["together", "shifted", "grad apart"])
+@pytest.mark.parametrize("shift", [0, 3, 7])
+@pytest.mark.parametrize("goff", [5, (1 << 16) - 300])
+def test_bf16_state_segments(bases, shift, goff):
+    _check_bf16_state(bases, shift, goff)
+
+
+@pytest.mark.parametrize("bases", list(BASES))
+@pytest.mark.parametrize("shift", [0, 5])
+def test_without_a_workspace(bases, shift):
+    """The kernels of calls without a workspace: longer tiles, whose shares go straight
+    to the result slots."""
+    _check_binary32(bases, shift, (1 << 32) - 9000, use_workspace=False)
+    if bases != "copy apart":
+        _check_bf16_state(bases, shift, (1 << 16) - 300, use_workspace=False)

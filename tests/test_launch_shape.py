@@ -1,6 +1,9 @@
 """The order in which blocks take tiles (dealt_tile in kernels.hip, in Python):
 a permutation of the grid for every run and grid size, with each XCD's blocks in
 stretches of `run` neighbours inside the whole groups."""
+import os
+import subprocess
+
 import pytest
 
 XCDS = 8
@@ -22,3 +25,23 @@ def test_every_tile_is_taken_once(grid, run):
         for xcd in range(XCDS):
             mine = [tiles[b] for b in range(first + xcd, first + XCDS * run, XCDS)]
             assert mine == list(range(first + xcd * run, first + (xcd + 1) * run))
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    """The rules of launch.h, compiled for the host."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    exe = tmp_path_factory.mktemp("launch_rules") / "launch_rules"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(root, "paper_2609_18178_amd", "csrc"), "-o", str(exe),
+                    os.path.join(root, "tests", "native", "launch_rules.cpp")], check=True)
+    return lambda *args: subprocess.run([str(exe), *map(str, args)], capture_output=True, text=True,
+                                        check=True).stdout.split()
+
+
+@pytest.mark.parametrize("mode", range(7))
+@pytest.mark.parametrize("elems", [1, 100_003, 1 << 20, 3 << 20, 16 << 20, 453_001_472])
+def test_calls_without_a_workspace_take_long_tiles(rules, mode, elems):
+    """Each tile of such a call adds to the same word, so it has at least 4096 elements."""
+    assert int(rules("tile", mode, elems, 0)[0]) >= 4096
+    assert int(rules("tile", mode, elems, 1)[0]) in (1024, 4096)
