@@ -80,8 +80,7 @@ extern "C" {
 #define PACT_EALIGN (-2)   /* misaligned pointer */
 #define PACT_EOVERLAP (-3) /* two buffers overlap */
 #define PACT_ERANGE (-4)   /* an index reaches 2^56 (the tag bits): global_offset + numel > 2^56; or the
-                            * shard needs more than 2^24 - 1 tiles of 4096 elements (one launch grid),
-                            * or a segment of a binary32 commit 2^24 of 1024 (288 GiB of arrays) */
+                            * shard needs more than 2^24 - 1 tiles of 4096 elements (one launch grid) */
 #define PACT_EHIP (-5)     /* a HIP call failed; see pact_last_hip_error() */
 #define PACT_ESCRATCH (-6) /* pact_adamw_commit_static: more segments than its static scratch holds */
 

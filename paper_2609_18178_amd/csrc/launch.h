@@ -21,6 +21,10 @@ constexpr int kVec = 4;
 constexpr int kUnroll = 4;
 constexpr int kTile = kBlock * kVec * kUnroll;
 
+// A dispatch counts its work-items in 32 bits, so one launch holds at most
+// this many tiles.
+constexpr uint64_t kMaxTiles = UINT32_MAX / kBlock;
+
 // Digest partial sums: each result slot owns kLanes workspace lines of
 // kLaneStride words (256 bytes); a line begins with kNodesPerLane nodes of two
 // words: two sets each of a lane's node, of a slot's own (in lane 0's line; the
@@ -158,13 +162,17 @@ constexpr uint64_t small_up_to(Mode m) {
     }
 }
 
-// The form of a call over `elems` elements.  Without a workspace each tile adds its
-// share to the one result word, 12 ns per tile whatever else the call does, so its tiles
-// are the longest there are.  us per call of 1M and 453M elements without a workspace, in
-// tiles of 1024 and of 4096 elements: commit 17.1 / 11.2 and 5504 / 2420; of 1M and 3M,
-// state digest 16.1 / 9.2 and 40.0 / 15.0; BF16 commit of 16M 196 / 64.
-constexpr Form form_of(Mode m, uint64_t elems, bool workspace) {
-    if (!workspace) return binary32_commit(m) ? Form::Long : Form::Usual;
+// The form of a call over `elems` elements, `longest` of them in its longest segment.
+// A segment's tiles have to fit one launch: where those of a binary32 commit do not (17e9
+// elements), they are the longer ones, which the host's limit is stated in.  And without
+// a workspace each tile adds its share to the one result word, 12 ns per tile whatever
+// else the call does, so its tiles are the longest there are.  us per call of 1M and 453M
+// elements without a workspace, in tiles of 1024 and of 4096 elements: commit 17.1 / 11.2
+// and 5504 / 2420; of 1M and 3M, state digest 16.1 / 9.2 and 40.0 / 15.0; BF16 commit of
+// 16M 196 / 64.
+constexpr Form form_of(Mode m, uint64_t elems, uint64_t longest, bool workspace) {
+    const bool longer = !workspace || longest / shape_of(m, Form::Usual).elems() >= kMaxTiles;
+    if (longer) return binary32_commit(m) ? Form::Long : Form::Usual;
     return elems <= small_up_to(m) ? Form::Small : Form::Usual;
 }
 

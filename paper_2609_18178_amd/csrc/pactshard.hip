@@ -33,9 +33,7 @@ thread_local int g_last_hip_error = 0;
 
 constexpr uint64_t kIndexLimit = 1ull << 56;  // indices must stay below the tag bits
 constexpr uint32_t kMaxSegments = 1u << 24;     // keeps every slot and lane index in 32 bits
-// A dispatch counts its work-items in 32 bits, so one launch holds at most
-// this many tiles.
-constexpr uint64_t kMaxTiles = UINT32_MAX / pact::kBlock;
+using pact::kMaxTiles;
 
 int fail_hip(hipError_t e) {
     g_last_hip_error = static_cast<int>(e);
@@ -366,17 +364,19 @@ struct Tiling {
     uint32_t passes;  // of the form's shape in a tile
     uint64_t elems;   // of a tile
     uint64_t tiles;   // of the call
-    bool fits;        // every segment's tiles fit one launch
 };
 
 Tiling tiling_of(pact::Mode mode, const View& s, size_t nwork) {
-    uint64_t elems = s.numel;
+    uint64_t elems = s.numel, longest = s.numel;
     if (s.segs != nullptr) {
-        elems = 0;
-        for (size_t k = 0; k < nwork; ++k) elems += s.segs[k].length;
+        elems = longest = 0;
+        for (size_t k = 0; k < nwork; ++k) {
+            elems += s.segs[k].length;
+            longest = std::max(longest, s.segs[k].length);
+        }
     }
     Tiling t;
-    t.form = pact::form_of(mode, elems, s.workspace != nullptr);
+    t.form = pact::form_of(mode, elems, longest, s.workspace != nullptr);
     const uint64_t pass = pact::shape_of(mode, t.form).elems();
     t.passes = 1;
     if (t.form == pact::Form::Usual && (mode == pact::Mode::Bf16Digest || mode == pact::Mode::DigestBf16State)) {
@@ -390,11 +390,8 @@ Tiling tiling_of(pact::Mode mode, const View& s, size_t nwork) {
     }
     t.elems = pass * t.passes;
     t.tiles = 0;
-    t.fits = true;
     auto add = [&](uint64_t first, uint64_t count) {
-        const uint64_t n = tiles_of(count, align_of(mode, s, first), t.elems);
-        t.tiles += n;
-        t.fits = t.fits && n <= kMaxTiles;
+        t.tiles += tiles_of(count, align_of(mode, s, first), t.elems);
     };
     if (s.segs == nullptr) add(0, s.numel);
     for (size_t k = 0; s.segs != nullptr && k < nwork; ++k) add(s.segs[k].offset, s.segs[k].length);
@@ -430,7 +427,6 @@ int enqueue(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out
     res.total_tiles = 0;
     const size_t nwork = work.count();
     const Tiling t = tiling_of(mode, s, nwork);
-    if (!t.fits) return PACT_ERANGE;
     if (per_segment && res.words != nullptr && t.tiles <= pact::kGatherTiles) res.total_tiles = (uint32_t)t.tiles;
     hipError_t e = hipSuccess;
     if (!(ws.clean && res.words != nullptr)) {
@@ -474,7 +470,7 @@ int enqueue(pact::Mode mode, const View& s, const SegSource& work, uint64_t* out
             const SegWork w = work.at(first + cnt);
             const uint32_t align = align_of(mode, s, w.first);
             const uint64_t n = tiles_of(w.count, align, t.elems);
-            if (tiles + n > kMaxTiles) break;
+            if (tiles + n > kMaxTiles) break;  // (n alone is not: validate and form_of see to it)
             pact::Segment& sg = b.seg[cnt];
             sg.tile_begin = b.tile_begin[cnt] = (uint32_t)tiles;
             tiles += n;

@@ -43,5 +43,17 @@ def rules(tmp_path_factory):
 @pytest.mark.parametrize("elems", [1, 100_003, 1 << 20, 3 << 20, 16 << 20, 453_001_472])
 def test_calls_without_a_workspace_take_long_tiles(rules, mode, elems):
     """Each tile of such a call adds to the same word, so it has at least 4096 elements."""
-    assert int(rules("tile", mode, elems, 0)[0]) >= 4096
-    assert int(rules("tile", mode, elems, 1)[0]) in (1024, 4096)
+    assert int(rules("tile", mode, elems, elems, 0)[0]) >= 4096
+    assert int(rules("tile", mode, elems, elems, 1)[0]) in (1024, 4096)
+
+
+@pytest.mark.parametrize("mode", [0, 3])
+def test_commits_of_the_longest_segments_fit_a_launch(rules, mode):
+    """A segment of up to 2^24 - 1 tiles of 4096 elements fits one launch, also where its
+    usual tiles, of 1024, would not."""
+    most = 2 ** 24 - 1
+    assert int(rules("tile", mode, most * 1024 - 1, most * 1024 - 1, 1)[0]) == 1024
+    assert int(rules("tile", mode, most * 2048, most * 1024 - 1, 1)[0]) == 1024  # several segments: several launches
+    for longest in (most * 1024 + 1, 2 ** 24 * 1024, most * 4096):
+        elems = int(rules("tile", mode, longest, longest, 1)[0])
+        assert -(-longest // elems) <= most
