@@ -122,7 +122,8 @@ struct Shape {
 enum class Form : int { Usual, Small, Long };
 
 // The commits of binary32 state move one row of 4 KB per array (the comment at
-// kReserveLds in kernels.hip says why), or four (Long); the others' kernels, bound by
+// kReserveLds in kernels.hip says why), or four (Long; the state digest's Long tiles have
+// several passes); the others' kernels, bound by
 // reading or by VALU issue, have more loads in flight per thread, and a second shape of
 // one short row for shards that would leave most of the GPU idle (Small).
 constexpr Shape shape_of(Mode m, Form f) {
@@ -144,6 +145,7 @@ constexpr Shape shape_of(Mode m, Form f) {
 }
 
 constexpr bool binary32_commit(Mode m) { return m == Mode::Commit || m == Mode::CommitZeroGrad; }
+constexpr bool has_long(Mode m) { return binary32_commit(m) || m == Mode::StateDigest; }
 
 // Elements up to which the small shape is the faster one (0: there is none).
 // us per call, small / large shape, at 0.1M, 1M, 4M and 16M elements:
@@ -162,6 +164,13 @@ constexpr uint64_t small_up_to(Mode m) {
     }
 }
 
+// State digests of this many elements and more hand in once for four passes.  Each
+// hand-in holds a wave slot for the answer of an atomic, but long tiles leave the GPU
+// emptier at the end.  us in tiles of one / four passes: 220M elements 442.7 / 444.4, 300M
+// 604.7 / 603.3, 453M 918.9 / 916.9, 700M 1420.9 / 1413.4, 1800M 3667 / 3629.
+constexpr uint64_t kLongDigestFrom = 3u << 27;
+constexpr uint32_t kLongDigestPasses = 4;
+
 // The form of a call over `elems` elements, `longest` of them in its longest segment.
 // A segment's tiles have to fit one launch: where those of a binary32 commit do not (17e9
 // elements), they are the longer ones, which the host's limit is stated in.  And without
@@ -173,6 +182,7 @@ constexpr uint64_t small_up_to(Mode m) {
 constexpr Form form_of(Mode m, uint64_t elems, uint64_t longest, bool workspace) {
     const bool longer = !workspace || longest / shape_of(m, Form::Usual).elems() >= kMaxTiles;
     if (longer) return binary32_commit(m) ? Form::Long : Form::Usual;
+    if (m == Mode::StateDigest && elems >= kLongDigestFrom) return Form::Long;
     return elems <= small_up_to(m) ? Form::Small : Form::Usual;
 }
 

@@ -378,14 +378,13 @@ Tiling tiling_of(pact::Mode mode, const View& s, size_t nwork) {
     Tiling t;
     t.form = pact::form_of(mode, elems, longest, s.workspace != nullptr);
     const uint64_t pass = pact::shape_of(mode, t.form).elems();
-    t.passes = 1;
+    t.passes = mode == pact::Mode::StateDigest && t.form == pact::Form::Long ? pact::kLongDigestPasses : 1;
     if (t.form == pact::Form::Usual && (mode == pact::Mode::Bf16Digest || mode == pact::Mode::DigestBf16State)) {
         // The 16-bit digests spend a few percent of a short tile on its start
         // and end: two passes once 8192 tiles are left, four likewise (bf16
         // digest of 76M and 453M elements 48.8 -> 47.0 and 263 -> 242 us, BF16
         // state digest 121.5 -> 119.8 and 698 -> 685; of 16M, with fewer tiles
-        // than that, 13.3 -> 13.4 and 28.6 -> 29.7).  The state digest and the
-        // commits gain nothing from it.
+        // than that, 13.3 -> 13.4 and 28.6 -> 29.7).
         while (t.passes < 4 && elems / (pass * t.passes * 2) >= 8192) t.passes *= 2;
     }
     t.elems = pass * t.passes;
