@@ -33,7 +33,9 @@ def _clear(sh):
     return int(sh.workspace.count_nonzero().item()) == 0
 
 
-@pytest.mark.parametrize("n", [0, 1, T, 63 * T, 64 * T, 64 * T + 1, 65 * T + 5, 80 * T, 1040 * T + 17])
+# tiles of T elements in the guard, and of T / 4 in the state digest up to 3M
+@pytest.mark.parametrize("n", [0, 1, T, 63 * T // 4, 16 * T, 16 * T + 1, 65 * T // 4 + 5, 63 * T, 64 * T, 64 * T + 1, 65 * T + 5,
+                               80 * T, 1040 * T + 17])
 def test_flat_slot_at_every_tile_count(n):
     pk = _pk()
     p, g, m, v = _state(n, 1)
@@ -67,8 +69,8 @@ def test_segment_slots_and_total(lengths):
 
 @pytest.mark.parametrize("n", [3 * T + 7, 70 * T])
 def test_call_after_a_workspace_that_was_not_clear(n):
-    """A workspace written to while its state says clear costs one call; a
-    caller that says so costs none."""
+    """A workspace written to while its state says clear costs the digest nothing, and
+    neither does one that the caller says it has written to."""
     import torch
 
     pk = _pk()
