@@ -970,19 +970,11 @@ __device__ __forceinline__ uint64_t do_row(const Arrays& a, uint64_t e0, uint32_
 // (kernel arguments, scalar loads); the tile's digest share is summed over the
 // workgroup in LDS and handed in with a 64-bit atomic for each of two words.
 // ---------------------------------------------------------------------------
-// The tile of this block, with runs of `run` tiles per XCD; the blocks behind
-// the last whole group keep their order.
-__device__ __forceinline__ uint32_t dealt_tile(uint32_t tiles, uint32_t run) {
-    const uint32_t group = kXcds * run;
-    const uint32_t r = blockIdx.x % group, first = blockIdx.x - r;
-    return tiles - first >= group ? first + r % kXcds * run + r / kXcds : blockIdx.x;
-}
-
 template <Mode M, Form F>
 __device__ __forceinline__ uint32_t tile_of_block(uint32_t tiles) {
     constexpr Runs kRuns = runs_of(M, F);
-    if (tiles >= kRuns.long_from) return dealt_tile(tiles, kRuns.long_run);
-    if (tiles >= kRuns.from) return dealt_tile(tiles, kRuns.run);
+    if (tiles >= kRuns.long_from) return dealt_tile(blockIdx.x, tiles, kRuns.long_run);
+    if (tiles >= kRuns.from) return dealt_tile(blockIdx.x, tiles, kRuns.run);
     return blockIdx.x;
 }
 

@@ -213,6 +213,14 @@ constexpr Runs runs_of(Mode m, Form f) {
     }
 }
 
+// The tile of a block, with runs of `run` tiles per XCD; the blocks behind the last
+// whole group keep their order.
+constexpr uint32_t dealt_tile(uint32_t block, uint32_t tiles, uint32_t run) {
+    const uint32_t group = kXcds * run;
+    const uint32_t r = block % group, first = block - r;
+    return tiles - first >= group ? first + r % kXcds * run + r / kXcds : block;
+}
+
 // Enqueue the clearing of what the tile kernels hand their shares in to: the
 // nodes of nres result slots when `words` is given, else the nslots digest slots.
 hipError_t launch_clear(uint64_t* digest, uint64_t* words, uint32_t nres, uint32_t nslots, hipStream_t stream);

@@ -1,6 +1,7 @@
-"""The order in which blocks take tiles (dealt_tile in kernels.hip, in Python):
-a permutation of the grid for every run and grid size, with each XCD's blocks in
-stretches of `run` neighbours inside the whole groups."""
+"""The launch rules of csrc/launch.h, compiled for the host (tests/native/launch_rules.cpp):
+the order in which blocks take tiles, a permutation of the grid for every run and grid size
+with each XCD's blocks in stretches of `run` neighbours inside the whole groups; and the
+tiles that a call is cut into."""
 import os
 import subprocess
 
@@ -9,27 +10,8 @@ import pytest
 XCDS = 8
 
 
-def dealt(block, grid, run):
-    group = XCDS * run
-    r = block % group
-    first = block - r
-    return first + r % XCDS * run + r // XCDS if grid - first >= group else block
-
-
-@pytest.mark.parametrize("run", [16, 32, 128])
-@pytest.mark.parametrize("grid", [1, 7, 8, 127, 128, 129, 255, 256, 257, 1023, 1024, 1025, 2048, 2500, 32768, 40001])
-def test_every_tile_is_taken_once(grid, run):
-    tiles = [dealt(b, grid, run) for b in range(grid)]
-    assert sorted(tiles) == list(range(grid))
-    for first in range(0, grid - XCDS * run + 1, XCDS * run):
-        for xcd in range(XCDS):
-            mine = [tiles[b] for b in range(first + xcd, first + XCDS * run, XCDS)]
-            assert mine == list(range(first + xcd * run, first + (xcd + 1) * run))
-
-
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
-    """The rules of launch.h, compiled for the host."""
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     exe = tmp_path_factory.mktemp("launch_rules") / "launch_rules"
     subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
@@ -37,6 +19,17 @@ def rules(tmp_path_factory):
                     os.path.join(root, "tests", "native", "launch_rules.cpp")], check=True)
     return lambda *args: subprocess.run([str(exe), *map(str, args)], capture_output=True, text=True,
                                         check=True).stdout.split()
+
+
+@pytest.mark.parametrize("run", [16, 32, 128])
+@pytest.mark.parametrize("grid", [1, 7, 8, 127, 128, 129, 255, 256, 257, 1023, 1024, 1025, 2048, 2500, 32768, 40001])
+def test_every_tile_is_taken_once(rules, grid, run):
+    tiles = [int(x) for x in rules("dealt", grid, run)]
+    assert sorted(tiles) == list(range(grid))
+    for first in range(0, grid - XCDS * run + 1, XCDS * run):
+        for xcd in range(XCDS):
+            mine = [tiles[b] for b in range(first + xcd, first + XCDS * run, XCDS)]
+            assert mine == list(range(first + xcd * run, first + (xcd + 1) * run))
 
 
 @pytest.mark.parametrize("mode", range(7))
