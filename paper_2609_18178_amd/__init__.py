@@ -119,13 +119,8 @@ def _lib():
         lib.pact_adamw_commit_bf16.restype = ctypes.c_int
         lib.pact_shard_digest_bf16.argtypes = [PB]
         lib.pact_shard_digest_bf16.restype = ctypes.c_int
-        W, H, u64 = ctypes.POINTER(_CWorkspaceState), ctypes.POINTER(_CHyper), ctypes.c_uint64
-        for name, args in (("adamw_commit", [P, u64, H, ctypes.c_uint32]), ("grad_guard", [P, ctypes.c_void_p]),
-                           ("shard_digest", [P]), ("bf16_digest", [P, ctypes.c_void_p]),
-                           ("adamw_commit_bf16", [PB, u64, H]), ("shard_digest_bf16", [PB])):
-            f = getattr(lib, f"pact_{name}_ws")
-            f.argtypes, f.restype = args + [W], ctypes.c_int
         # the entry points of the calls below, which pass the shard as bytes
+        W, H, u64 = ctypes.POINTER(_CWorkspaceState), ctypes.POINTER(_CHyper), ctypes.c_uint64
         V, packed = ctypes.c_void_p, {}
         for name, args in (("adamw_commit_ws", [u64, H, ctypes.c_uint32, W]),
                            ("adamw_commit_static", [u64, H, ctypes.c_uint32]),

@@ -36,6 +36,9 @@ int main(void) {
     OPEN(pact_arena_layout);
     F(pact_arena_layout, pool_bytes); F(pact_arena_layout, spacing); F(pact_arena_layout, offset);
     CLOSE();
+    OPEN(pact_workspace_state);
+    F(pact_workspace_state, stream); F(pact_workspace_state, clear); F(pact_workspace_state, odd);
+    CLOSE();
     printf(", \"codes\": {\"PACT_ARENA_SPACING\": %llu, \"PACT_ARENA_PACK_BELOW\": %llu, ",
            (unsigned long long)PACT_ARENA_SPACING, (unsigned long long)PACT_ARENA_PACK_BELOW);
     printf("\"PACT_OK\": %d, \"PACT_EINVAL\": %d, \"PACT_EALIGN\": %d, \"PACT_EOVERLAP\": %d, "

@@ -240,7 +240,7 @@ def test_header_is_c99_and_matches_the_binding(tmp_path):
                     "-o", str(exe), os.path.join(root, "tests", "native", "abi_layout.c")], check=True)
     c = json.loads(subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout)
     mirrors = {"pact_hyper": pk._CHyper, "pact_segment": pk._CSegment, "pact_shard": pk._CShard,
-               "pact_shard_bf16": pk._CShardBf16, "pact_arena_layout": pk._CArenaLayout}
+               "pact_shard_bf16": pk._CShardBf16, "pact_arena_layout": pk._CArenaLayout, "pact_workspace_state": pk._CWorkspaceState}
     for name, cls in mirrors.items():
         assert ctypes.sizeof(cls) == c[name]["sizeof"], name
         py_fields = {f[0]: getattr(cls, f[0]).offset for f in cls._fields_}
