@@ -51,8 +51,8 @@ def parse():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-probe", action="store_true")
     ap.add_argument("--no-parity", action="store_true", help="skip the in-run oracle replay of the timed commits")
-    ap.add_argument("--record-valu-ceiling", action="store_true",
-                    help="also write profiles/valu_ceiling_<kernel>.json from this run's cache-resident timings")
+    ap.add_argument("--record-cache-resident", action="store_true",
+                    help="also write profiles/cache_resident_<kernel>.json from this run's cache-resident timings")
     ap.add_argument("--layout", choices=("spread", "packed"), default="spread",
                     help="spread: the five arrays in one ShardArena pool, each in its own region of HBM "
                          "(the library's recommended placement); packed: five separate allocations")
@@ -236,13 +236,24 @@ def _cpu_model() -> str:
     return "unknown"
 
 
-# rocprofv3 kernel names -> the names bench.py reports them under, bytes per
-# element, and elements of a workgroup (one tile) on a large shard
-CLOCK_KERNELS = (("tile_kernel<(pact::Mode)0", "commit", 30, 1024), ("probe_kernel(", "probe", 30, 4096),
-                 ("tile_kernel<(pact::Mode)3", "commit_zero_grad", 34, 1024),
-                 ("tile_kernel<(pact::Mode)4", "grad_guard", 4, 4096),
-                 ("tile_kernel<(pact::Mode)1", "shard_digest", 12, 4096),
-                 ("tile_kernel_bf16<(pact::Mode)5", "commit_bf16_state", 14, 4096))
+# rocprofv3 kernel names -> the names bench.py reports them under, and bytes per element
+CLOCK_KERNELS = (("tile_kernel<(pact::Mode)0", "commit", 30), ("probe_kernel(", "probe", 30),
+                 ("tile_kernel<(pact::Mode)3", "commit_zero_grad", 34),
+                 ("tile_kernel<(pact::Mode)4", "grad_guard", 4),
+                 ("tile_kernel<(pact::Mode)1", "shard_digest", 12),
+                 ("tile_kernel_bf16<(pact::Mode)5", "commit_bf16_state", 14))
+
+
+def tile_elements(kernel: str, n: int) -> int:
+    """Elements of one workgroup of a kernel on a large shard of n elements."""
+    if kernel in ("commit", "commit_zero_grad"):
+        return 1024
+    return 4 * 4096 if kernel == "shard_digest" and n >= 3 << 27 else 4096
+
+
+# Sub-shards of the cache-resident rates: name, bytes per element moved and resident, sizes
+RESIDENT = (("shard_digest", 12, 12, (4 << 20, 8 << 20, 12 << 20, 16 << 20)),
+            ("commit_bf16_state", 14, 8, (17 << 20, 20 << 20, 23 << 20, 26 << 20)))
 XCDS = 8      # GRBM_GUI_ACTIVE comes back summed over the eight XCDs
 NUM_CUS = 256
 # Nominal VALU issue peak: 256 CUs x 4 SIMDs, each SIMD 16 lanes wide, so one
@@ -264,12 +275,12 @@ def record_clock(workload: str, clock_csv: str) -> dict:
     disp = {}
     with open(clock_csv) as f:
         for row in csv.DictReader(f):
-            hit = [(key, bpe, tile) for pat, key, bpe, tile in CLOCK_KERNELS if pat in row["Kernel_Name"]]
+            hit = [(key, bpe) for pat, key, bpe in CLOCK_KERNELS if pat in row["Kernel_Name"]]
             if not hit:
                 continue
-            full_grid = -(-n // hit[0][2]) * 256  # work-items of one full-shard launch (256 threads per tile)
+            full_grid = -(-n // tile_elements(hit[0][0], n)) * 256  # work-items of one full-shard launch
             if int(row.get("Grid_Size", full_grid)) != full_grid:
-                continue  # other kernels, and the sub-shard launches of the VALU-ceiling timing
+                continue  # other kernels, and the sub-shard launches of the cache-resident timing
             d = disp.setdefault(int(row["Dispatch_Id"]), {"key": hit[0][0], "bpe": hit[0][1]})
             d[row["Counter_Name"]] = float(row["Counter_Value"])
             d["dur_s"] = (int(row["End_Timestamp"]) - int(row["Start_Timestamp"])) * 1e-9
@@ -323,7 +334,7 @@ def stored_traffic(workload: str, src_hash: str):
 def launch_shape(w, args) -> dict:
     """The 30 B/element stream probe on the workload's arrays (spread layout,
     zero-filled: the probe's cost does not depend on the values), launched
-    with one workgroup per tile (the kernels' shape) and from persistent
+    with one workgroup per tile (as every kernel is) and from persistent
     grids of 1-16 workgroups per CU striding over the tiles; median of 20
     launches per shape, four rounds in alternating order, best round kept."""
     import torch
@@ -584,12 +595,13 @@ def main():
             print(f"[bench] {name}: {ms:.4f} ms (median {med:.4f}), {extra[name]['gbps']:.1f} GB/s at {bpe} B/element",
                   file=sys.stderr, flush=True)
 
-        # VALU ceilings of the two VALU-heavy kernels: the same kernel on
-        # sub-shards small enough to stay in the 256 MB Infinity Cache, at two
-        # sizes; the slope of launch time over elements is the kernel's rate
-        # when HBM does not limit it (launch and tail costs cancel in the
-        # difference).  frac = the full-size time that rate allows / the
-        # measured full-size time.
+        # Rates of the two VALU-heavy modes when HBM does not limit them: sub-shards
+        # small enough to stay in the 256 MB Infinity Cache, at four sizes, and the
+        # slope of launch time over elements (launch and tail costs cancel in it).
+        # The BF16 commit runs the kernel of its full size there; the state digest the
+        # usual one, of one pass a tile, since no shard of the four-pass kernel's sizes
+        # fits the cache.  frac = the full-size time at that rate / the measured one: the
+        # short launches do not fill the GPU as well, so it may pass 1 and is no ceiling.
         def subshard_fn(name, m):
             if name == "shard_digest":
                 ss = pk.Shard(tensors[0][:m], None, tensors[2][:m], tensors[3][:m], None,
@@ -603,8 +615,7 @@ def main():
                 st[0] += 1
             return f
 
-        sub_sizes = (1 << 22, 2 << 22, 3 << 22, 4 << 22)
-        for name, bpe, ws in (("shard_digest", 12, 12), ("commit_bf16_state", 14, 8)):
+        for name, bpe, ws, sub_sizes in RESIDENT:
             if name not in extra or sub_sizes[-1] > n:
                 continue
             ts = [median_launch(subshard_fn(name, m), 40, settle_s=SETTLE_S / 2) for m in sub_sizes]
@@ -616,22 +627,24 @@ def main():
                      / sum((x - mx) ** 2 for x in sub_sizes))  # ms per element
             rate = 1e3 / slope
             full_ms = extra[name]["median_launch_ms"]
-            ceil = {"elements_per_s": rate, "full_size_ms_at_ceiling": n / rate * 1e3,
-                    "frac": (n / rate * 1e3) / full_ms,
-                    "bytes_per_s_at_ceiling": rate * bpe,
-                    "sizes": list(sub_sizes), "median_launch_ms": ts,
-                    "working_set_bytes": sub_sizes[-1] * ws,
-                    "method": "least-squares slope of the median launch time over four cache-resident "
-                              "sub-shards (same kernel, same instruction mix); frac = full-size time at that "
-                              "rate / measured full-size median launch time"}
-            extra[name]["valu_ceiling"] = ceil
+            rec = {"elements_per_s": rate, "full_size_ms_at_this_rate": n / rate * 1e3,
+                   "frac": (n / rate * 1e3) / full_ms,
+                   "bytes_per_s_at_this_rate": rate * bpe,
+                   "sizes": list(sub_sizes), "median_launch_ms": ts,
+                   "working_set_bytes": sub_sizes[-1] * ws,
+                   "method": "least-squares slope of the median launch time over four cache-resident "
+                             "sub-shards" + (" (in tiles of one pass, the full size's have four)"
+                                             if tile_elements(name, n) != tile_elements(name, sub_sizes[-1]) else "")
+                             + "; frac = full-size time at that rate / measured full-size median launch time (the "
+                               "short launches fill the GPU less well: no ceiling)"}
+            extra[name]["cache_resident"] = rec
             print(f"[bench] {name}: cache-resident rate {rate:.3e} elem/s -> {n / rate * 1e3:.4f} ms at full size, "
-                  f"frac {ceil['frac']:.3f} of that ceiling", file=sys.stderr, flush=True)
-            if args.record_valu_ceiling:
-                rec = dict(ceil, kernel=name, workload=w.name, full_size_elements=n, full_size_median_ms=full_ms,
+                  f"{rec['frac']:.3f} of the measured time", file=sys.stderr, flush=True)
+            if args.record_cache_resident:
+                rec = dict(rec, kernel=name, workload=w.name, full_size_elements=n, full_size_median_ms=full_ms,
                            kernel_source_hash=kernel_source_hash(),
-                           command=f"python bench.py --workload {w.name} --record-valu-ceiling")
-                with open(os.path.join(ROOT, "profiles", f"valu_ceiling_{name}.json"), "w") as fh:
+                           command=f"python bench.py --workload {w.name} --record-cache-resident")
+                with open(os.path.join(ROOT, "profiles", f"cache_resident_{name}.json"), "w") as fh:
                     json.dump(rec, fh, indent=1)
                     fh.write("\n")
 
@@ -743,8 +756,8 @@ def main():
             "median_launch_ms": main_m["median_launch_ms"],
             "min_launch_ms": main_m["min_launch_ms"],
             "valu": valu_of("commit"),
-            # the same 30 B/element pattern with no arithmetic, in the same run:
-            # the practical ceiling of the access pattern (context, not the metric)
+            # the same 30 B/element with no arithmetic, in the same run: a fixed reference
+            # (tiles of 16 KB per array in plain order; the commit's may beat it)
             "frac_of_probe": (achieved / probe_res["gbps"]) if probe_res else None,
             "timing": "hipEvents around each commit call on the launch stream; a call is its tile launches alone "
                       "(one per 32 segments), whose last workgroup writes the digest",

@@ -113,3 +113,35 @@ def test_oracle_replay_matches_a_direct_run_and_sees_a_wrong_digest():
     assert r["match"] and r["oracle_digest"] == f"{d:#018x}"
     assert not bench.oracle_replay(w, [100, 101, 102], d ^ 1, threads=2, chunk=70_001)["match"]
     assert not bench.oracle_replay(w, [100, 101], d, threads=2)["match"]
+
+
+def test_record_clock_counts_full_size_launches_only(sandbox):
+    """Kernels are told apart by mode, and a full-size launch by its grid: the state digest's
+    tiles have four passes at this size, the commit's one row; sub-shards are left out."""
+    rows = []
+    for d, (name, tile, n) in enumerate([("void pact::tile_kernel<(pact::Mode)1, (pact::Form)2>(a)", 16384, N),
+                                         ("void pact::tile_kernel<(pact::Mode)1, (pact::Form)0>(a)", 4096, 16 << 20),
+                                         ("void pact::tile_kernel<(pact::Mode)0, (pact::Form)0>(a)", 1024, N),
+                                         ("void pact::tile_kernel_bf16<(pact::Mode)5, (pact::Form)0>(a)", 4096, N),
+                                         ("void pact::tile_kernel_bf16<(pact::Mode)5, (pact::Form)0>(a)", 4096, 17 << 20)]):
+        for cname in ("GRBM_GUI_ACTIVE", "SQ_INSTS_VALU"):
+            rows.append({"Dispatch_Id": d, "Kernel_Name": name, "Counter_Name": cname, "Counter_Value": 1e7,
+                         "Start_Timestamp": 0, "End_Timestamp": 1000, "Grid_Size": -(-n // tile) * 256})
+    with open(sandbox / "c.csv", "w", newline="") as f:
+        w = csv.DictWriter(f, fieldnames=FIELDS + ["Grid_Size"])
+        w.writeheader()
+        w.writerows(rows)
+    kernels = bench.record_clock("mistral7b_shard16", str(sandbox / "c.csv"))["kernels"]
+    assert {k: r["dispatches"] for k, r in kernels.items()} == {"shard_digest": 1, "commit": 1, "commit_bf16_state": 1}
+
+
+def test_cache_resident_sizes_run_the_kernels_they_stand_for():
+    """The sub-shards of the cache-resident rates lie above the small kernels' sizes (launch.h) and
+    inside the 256 MB cache."""
+    src = open(os.path.join(ROOT, "paper_2609_18178_amd", "csrc", "launch.h")).read()
+    for line in ("case Mode::StateDigest: return 3u << 20;", "case Mode::CommitBf16State: return 16u << 20;"):
+        assert line in src
+    for name, _, bytes_resident, sizes in bench.RESIDENT:
+        assert min(sizes) > {"shard_digest": 3 << 20, "commit_bf16_state": 16 << 20}[name]
+        assert max(sizes) * bytes_resident <= 256e6
+    assert bench.tile_elements("shard_digest", (3 << 27) - 1) == 4096 and "kLongDigestFrom = 3u << 27" in src
