@@ -30,7 +30,11 @@ GEN_FLAGS    := -O3 -std=c11 -fopenmp -fPIC -shared -Wall -Wextra
 C_CALLER := tests/native/c_caller
 ROCM     ?= /opt/rocm
 
-all: oracle/liboracle.so workloads/libgen.so $(if $(LIB_SRCS),$(LIB) $(C_CALLER),)
+# How far the hardware's reciprocal and square root are from the correctly
+# rounded ones (test infrastructure; the library's own floating-point flags).
+HW_APPROX := tests/native/hw_approx
+
+all: oracle/liboracle.so workloads/libgen.so $(if $(LIB_SRCS),$(LIB) $(C_CALLER) $(HW_APPROX),)
 
 oracle/liboracle.so: oracle/oracle.c oracle/oracle.h
 	$(CC) $(ORACLE_FLAGS) -o $@ oracle/oracle.c -lm
@@ -47,6 +51,9 @@ $(C_CALLER): tests/native/c_caller.c include/pactshard.h oracle/oracle.h $(LIB) 
 	    -Wl,-rpath,'$$ORIGIN/../../$(PKG)' -Wl,-rpath,'$$ORIGIN/../../oracle' -Wl,-rpath,'$$ORIGIN/../../workloads' \
 	    -Wl,-rpath,$(ROCM)/lib
 
+$(HW_APPROX): tests/native/hw_approx.hip
+	$(HIPCC) $(filter-out -shared -fPIC,$(HIPFLAGS)) -o $@ $<
+
 # gfx950 assembly of the kernels, for inspection and the hazard test
 isa: _build/kernels-gfx950.s
 _build/kernels-gfx950.s: $(PKG)/csrc/kernels.hip $(LIB_HDRS)
@@ -54,7 +61,7 @@ _build/kernels-gfx950.s: $(PKG)/csrc/kernels.hip $(LIB_HDRS)
 	$(HIPCC) $(filter-out -shared -fPIC,$(HIPFLAGS)) --cuda-device-only -S -o $@ $(PKG)/csrc/kernels.hip
 
 clean:
-	rm -f $(LIB) oracle/liboracle.so workloads/libgen.so $(C_CALLER)
+	rm -f $(LIB) oracle/liboracle.so workloads/libgen.so $(C_CALLER) $(HW_APPROX)
 	rm -rf _build
 
 .PHONY: all clean isa
