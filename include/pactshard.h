@@ -272,7 +272,7 @@ int64_t pact_workspace_bytes_bf16(const pact_shard_bf16* s);
  * commit's eight concurrent streams (reads of p, g, m, v; writes of p', m',
  * v' and the bf16 copy) reach about 6.4-6.5 TB/s (80-81% of the 8 TB/s
  * peak) when the arrays sit in separate regions of HBM some tens of GB
- * apart, and about 5.6-5.7 TB/s (70-71%) when they sit within a few GB of
+ * apart, and about 6.1-6.2 TB/s (77-78%) when they sit within a few GB of
  * each other -- the case of five back-to-back allocations.  The kernels are
  * the same; the difference is the memory system's.  pact_arena_plan gives
  * the library's placement rule as byte offsets into one pool the caller
@@ -300,8 +300,9 @@ int pact_arena_plan(uint64_t numel, uint64_t spacing, pact_arena_layout* out);
 
 /* Measurement support, not part of the commit: streams the same bytes as a
  * commit (reads 4 fp32 arrays, writes 3 fp32 arrays and one 16-bit array,
- * 30 bytes per element) with no arithmetic beyond one add, so its rate is
- * the practical HBM ceiling of that access pattern.  out_* may alias in_*
+ * 30 bytes per element) with no arithmetic beyond one add, in tiles of 16 KB
+ * per array in plain order: a fixed reference for the commit's rate, which
+ * takes smaller tiles and may pass it.  out_* may alias in_*
  * element for element (in-place), as in a commit. */
 int pact_stream_probe(const float* in0, const float* in1, const float* in2, const float* in3,
                       float* out0, float* out2, float* out3, uint16_t* out_half,

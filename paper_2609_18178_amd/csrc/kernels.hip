@@ -425,8 +425,8 @@ __device__ __forceinline__ bool below(u16x2_t x, uint16_t limit) { return std::m
 // A NaN or an infinity anywhere leaves p' or v outside these ranges.  A row of a wave
 // with an element that fails takes the exact form.
 //
-// Bound by VALU issue and the clock it leaves: about 75 instructions per element
-// against 95 with the exact step.  453M elements 1195 -> 1104 us (5.7 TB/s), 76M 202 ->
+// Bound by VALU issue and the clock it leaves: 79.5 instructions per element (counted)
+// against 94.8 with the exact step.  453M elements 1187 -> 1120 us (5.7 TB/s), 76M 202 ->
 // 186, 6M 20.8 -> 19.0; fewer tiles in flight, 4 KB tiles and longer runs per XCD, which
 // the HBM-bound commits want, made no difference.
 template <int N>
@@ -1119,9 +1119,9 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
 // Waves per SIMD a kernel must be able to keep resident (caps its VGPRs).
 // The two standalone digests are bound by VALU issue and keep the full
 // eight waves per SIMD (the short index form would otherwise take the state
-// digest to 66 VGPRs and seven waves).  The BF16-state commit takes 64 VGPRs in
-// either case, scheduled for eight waves in its small shape (6M elements 18.6 us
-// against 19.6) and for six in the large one (453M 1115 us against 1128).
+// digest to 66 VGPRs and seven waves).  The BF16-state commit takes 41 VGPRs in its
+// small shape and 65 in the usual one, scheduled for eight waves in the former (6M
+// elements 18.6 us against 19.6) and for six in the latter (453M 1115 us against 1128).
 template <Mode M, Form F>
 constexpr unsigned kMinWavesPerSimd = (M == Mode::StateDigest || M == Mode::DigestBf16State) ? 8u
                                       : (M == Mode::CommitBf16State)                         ? (F == Form::Small ? 8u : 6u)
@@ -1176,9 +1176,10 @@ __global__ __launch_bounds__(kBlock) void total_kernel(uint64_t* digest, uint32_
     }
 }
 
-// 30 bytes per element with no arithmetic beyond one add, through the same
-// instructions and tile shape as the commit: the ceiling of the commit's
-// access pattern.  The outputs may alias the inputs element for element (in
+// 30 bytes per element with no arithmetic beyond one add, through the commit's
+// instructions in tiles of 16 KB per array in plain order: a fixed reference for
+// the commit's bytes (whose smaller tiles, with less in flight, may beat it where the
+// arrays lie close together).  The outputs may alias the inputs element for element (in
 // place).  n is a multiple of 4; the last tile's resources end at n, and a
 // vector beyond it is dropped by the buffer range check.
 __device__ __forceinline__ void probe_tile(const float* i0, const float* i1, const float* i2, const float* i3,
@@ -1219,7 +1220,7 @@ __device__ __forceinline__ void probe_tile(const float* i0, const float* i1, con
     }
 }
 
-// One workgroup per tile, as the commit launches.
+// One workgroup per tile.
 __global__ __launch_bounds__(kBlock) void probe_kernel(const float* i0, const float* i1, const float* i2,
                                                        const float* i3, float* o0, float* o2, float* o3,
                                                        uint16_t* oh, uint64_t n) {

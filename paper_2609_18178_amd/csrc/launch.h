@@ -15,8 +15,8 @@ constexpr int kSegsPerLaunch = 32;
 // Threads per workgroup (4 waves of 64).
 constexpr int kBlock = 256;
 
-// The stream probe's tile, the commit's: four 16-byte vectors of fp32 elements
-// per thread and array, 4096 elements.
+// The stream probe's tile: four 16-byte vectors of fp32 elements per thread and
+// array, 4096 elements.  Also the tile that the limit on a shard's size is stated in.
 constexpr int kVec = 4;
 constexpr int kUnroll = 4;
 constexpr int kTile = kBlock * kVec * kUnroll;
