@@ -137,7 +137,6 @@ constexpr Shape shape_of(Mode m, Form f) {
         case Mode::StateDigest:
             return small ? Shape{4, 1} : Shape{4, 4};
         case Mode::Bf16Digest:
-            return {8, 2};
         case Mode::CommitBf16State:
         case Mode::DigestBf16State:
             return small ? Shape{4, 1} : Shape{8, 2};
@@ -151,12 +150,14 @@ constexpr bool has_long(Mode m) { return binary32_commit(m) || m == Mode::StateD
 // Elements up to which the small shape is the faster one (0: there is none).
 // us per call, small / large shape, at 0.1M, 1M, 4M and 16M elements:
 //   state digest  4.1 / 5.3   6.0 / 6.4  12.8 / 12.8  42.4 / 38.9
+//   bf16 digest   3.6 / 3.6   4.9 / 4.5   8.6 / 6.0   22.0 / 13.5
 //   BF16 digest   4.0 / 5.0   5.7 / 6.0  12.0 / 11.4  37.8 / 32.0
 // and of the BF16 commit at 2M, 4M, 8M and 16M:
 //                 9.3 / 10.2 14.4 / 16.0 23.6 / 24.9  43.7 / 44.9
 constexpr uint64_t small_up_to(Mode m) {
     switch (m) {
         case Mode::StateDigest: return 3u << 20;
+        case Mode::Bf16Digest: return 1u << 19;
         case Mode::CommitBf16State: return 16u << 20;
         case Mode::DigestBf16State: return 3u << 19;
         default: return 0;
