@@ -691,6 +691,15 @@ template <Mode M, Form F>
 constexpr bool kManyPasses = M == Mode::StateDigest ? F == Form::Long
                                                     : F == Form::Usual && (M == Mode::Bf16Digest || M == Mode::DigestBf16State);
 
+// Kernels whose whole tiles branch around everything that only a tile with ragged ends
+// needs, which the others form in every tile.  us per state digest without / with it (and
+// of the form in which no tile had such ends): 76M elements 154.4 / 153.6 (154.2), 220M
+// 440.7 / 438.4 (437.7), 400M 801.3 / 797.1 (794.8).  Every other kernel is slower with it:
+// BF16 commit of 9.3M 26.7 -> 28.4 (25 scalar registers spilled instead of 10), guard,
+// digests and boundaries of a hundred and more short segments up to 8%.
+template <Mode M, Form F>
+constexpr bool kWholeApart = M == Mode::StateDigest && F != Form::Small;
+
 // Modes whose digest words have 16 bits (the short IndexLo16 form applies).
 template <Mode M>
 constexpr bool kWords16 = (M == Mode::Bf16Digest || M == Mode::CommitBf16State || M == Mode::DigestBf16State);
@@ -1034,15 +1043,10 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
         __hip_atomic_store(wave_sum, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     uint64_t acc = 0;
-    // What the tile has for the element-wise path: elements e, e + kBlock, ...
-    // below e_end.
-    uint64_t e = 0, e_end = 0;
-    if (align == kNeverAligned) {
-        e = e0 + threadIdx.x;
-        e_end = (e0 + tile_elems < seg_end) ? e0 + tile_elems : seg_end;
-    } else {
+    if constexpr (kWholeApart<M, F>) {
         const uint64_t left = e0 < seg_end ? seg_end - e0 : 0;
-        const uint32_t whole = left < tile_elems ? (uint32_t)left / kPass : passes;  // the tile's whole passes
+        uint32_t whole = left < tile_elems ? (uint32_t)left / kPass : passes;  // the tile's whole passes
+        if (align == kNeverAligned) whole = 0;
         auto one_pass = [&](uint64_t at) { acc += do_pass<M, kVecs, kRows>(a, at, sc); };
         if constexpr (kManyPasses<M, F>) {
 #pragma unroll 1
@@ -1050,31 +1054,77 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
         } else if (whole != 0) {
             one_pass(e0);
         }
-        const uint64_t at = e0 + whole * kPass;
-        if (whole < passes && at < seg_end) {
-            // The last pass of a segment: whole vectors, row by row, then the
-            // elements behind them.  (With every unaligned segment and every
-            // last tile element by element a rank's 20M-element slice of an
-            // unpadded vector took 156 us per zeroing commit and 76 + 44 us per
-            // BF16 commit and digest, against 125 and 58 + 34 us.)
-            const uint32_t nvec = (uint32_t)(seg_end - at) / kVecs;
+        if (whole < passes || (align != 0 && tile == sg.tile_begin)) {
+            // As below.
+            uint64_t e, e_end;
+            if (align == kNeverAligned) {
+                e = e0 + threadIdx.x;
+                e_end = (e0 + tile_elems < seg_end) ? e0 + tile_elems : seg_end;
+            } else {
+                e = e_end = 0;
+                const uint64_t at = e0 + whole * kPass;
+                if (whole < passes && at < seg_end) {
+                    const uint32_t nvec = (uint32_t)(seg_end - at) / kVecs;
 #pragma unroll 1
-            for (uint32_t done = 0; done < nvec; done += kBlock) {
-                acc += do_row<M, kVecs>(a, at + done * kVecs, nvec - done, sc);
+                    for (uint32_t done = 0; done < nvec; done += kBlock) {
+                        acc += do_row<M, kVecs>(a, at + done * kVecs, nvec - done, sc);
+                    }
+                    e = at + nvec * kVecs + threadIdx.x;
+                    e_end = seg_end;
+                }
+                if (tile == sg.tile_begin && threadIdx.x >= 64) {
+                    e = seg_first + threadIdx.x - 64;
+                    e_end = seg_first + align < seg_end ? seg_first + align : seg_end;
+                }
             }
-            e = at + nvec * kVecs + threadIdx.x;
-            e_end = seg_end;
-        }
-        if (tile == sg.tile_begin && threadIdx.x >= 64) {
-            // The first tile's second wave: the elements before the first
-            // aligned one (the segment may end among them).
-            e = seg_first + threadIdx.x - 64;
-            e_end = seg_first + align < seg_end ? seg_first + align : seg_end;
-        }
-    }
 #pragma unroll 1
-    for (; e < e_end; e += kBlock) {
-        acc += do_scalar<M>(a, e, sc);
+            for (; e < e_end; e += kBlock) {
+                acc += do_scalar<M>(a, e, sc);
+            }
+        }
+    } else {
+        // What the tile has for the element-wise path: elements e, e + kBlock, ...
+        // below e_end.
+        uint64_t e = 0, e_end = 0;
+        if (align == kNeverAligned) {
+            e = e0 + threadIdx.x;
+            e_end = (e0 + tile_elems < seg_end) ? e0 + tile_elems : seg_end;
+        } else {
+            const uint64_t left = e0 < seg_end ? seg_end - e0 : 0;
+            const uint32_t whole = left < tile_elems ? (uint32_t)left / kPass : passes;  // the tile's whole passes
+            auto one_pass = [&](uint64_t at) { acc += do_pass<M, kVecs, kRows>(a, at, sc); };
+            if constexpr (kManyPasses<M, F>) {
+#pragma unroll 1
+                for (uint32_t pass = 0; pass < whole; ++pass) one_pass(uniform(e0 + pass * kPass));
+            } else if (whole != 0) {
+                one_pass(e0);
+            }
+            const uint64_t at = e0 + whole * kPass;
+            if (whole < passes && at < seg_end) {
+                // The last pass of a segment: whole vectors, row by row, then the
+                // elements behind them.  (With every unaligned segment and every
+                // last tile element by element a rank's 20M-element slice of an
+                // unpadded vector took 156 us per zeroing commit and 76 + 44 us per
+                // BF16 commit and digest, against 125 and 58 + 34 us.)
+                const uint32_t nvec = (uint32_t)(seg_end - at) / kVecs;
+#pragma unroll 1
+                for (uint32_t done = 0; done < nvec; done += kBlock) {
+                    acc += do_row<M, kVecs>(a, at + done * kVecs, nvec - done, sc);
+                }
+                e = at + nvec * kVecs + threadIdx.x;
+                e_end = seg_end;
+            }
+            if (tile == sg.tile_begin && threadIdx.x >= 64) {
+                // The first tile's second wave: the elements before the first
+                // aligned one (the segment may end among them).
+                e = seg_first + threadIdx.x - 64;
+                e_end = seg_first + align < seg_end ? seg_first + align : seg_end;
+            }
+        }
+#pragma unroll 1
+        for (; e < e_end; e += kBlock) {
+            acc += do_scalar<M>(a, e, sc);
+        }
     }
     // Workgroup sum: every lane adds its share into its wave's LDS word with
     // one 64-bit LDS atomic (no VALU work: a shuffle tree costs about fifty

@@ -150,7 +150,8 @@ constexpr bool has_long(Mode m) { return binary32_commit(m) || m == Mode::StateD
 // Elements up to which the small shape is the faster one (0: there is none).
 // us per call, small / large shape, at 0.1M, 1M, 4M and 16M elements:
 //   state digest  4.1 / 5.3   6.0 / 6.4  12.8 / 12.8  42.4 / 38.9
-//   bf16 digest   3.6 / 3.6   4.9 / 4.5   8.6 / 6.0   22.0 / 13.5
+//   bf16 digest   3.6 / 3.6   4.9 / 4.5   8.6 / 6.0   22.0 / 13.5 (of 0.3M in 138 segments
+//                 21.9 / 24.0)
 //   BF16 digest   4.0 / 5.0   5.7 / 6.0  12.0 / 11.4  37.8 / 32.0
 // and of the BF16 commit at 2M, 4M, 8M and 16M:
 //                 9.3 / 10.2 14.4 / 16.0 23.6 / 24.9  43.7 / 44.9
@@ -166,8 +167,8 @@ constexpr uint64_t small_up_to(Mode m) {
 
 // State digests of this many elements and more hand in once for four passes.  Each
 // hand-in holds a wave slot for the answer of an atomic, but long tiles leave the GPU
-// emptier at the end.  us in tiles of one / four passes: 220M elements 442.7 / 444.4, 300M
-// 604.7 / 603.3, 453M 918.9 / 916.9, 700M 1420.9 / 1413.4, 1800M 3667 / 3629.
+// emptier at the end.  us in tiles of one / four passes: 220M elements 438.4 / 442.0, 300M
+// 597.9 / 599.2, 400M 797.1 / 797.4, 453M 905.4 / 901.4, 1800M 3612 / 3587.
 constexpr uint64_t kLongDigestFrom = 3u << 27;
 constexpr uint32_t kLongDigestPasses = 4;
 
