@@ -425,7 +425,7 @@ __device__ __forceinline__ bool below(u16x2_t x, uint16_t limit) { return std::m
 // A NaN or an infinity anywhere leaves p' or v outside these ranges.  A row of a wave
 // with an element that fails takes the exact form.
 //
-// Bound by VALU issue and the clock it leaves: 79.5 instructions per element (counted)
+// Bound by VALU issue and the clock it leaves: 79.9 instructions per element (counted)
 // against 94.8 with the exact step.  453M elements 1187 -> 1120 us (5.7 TB/s), 76M 202 ->
 // 186, 6M 20.8 -> 19.0; fewer tiles in flight, 4 KB tiles and longer runs per XCD, which
 // the HBM-bound commits want, made no difference.
@@ -1164,8 +1164,8 @@ __device__ __forceinline__ void tile_body(const A& a, const Batch& bt, uint64_t*
 // Waves per SIMD a kernel must be able to keep resident (caps its VGPRs).
 // The two standalone digests are bound by VALU issue and keep the full
 // eight waves per SIMD (the short index form would otherwise take the state
-// digest to 66 VGPRs and seven waves).  The BF16-state commit takes 41 VGPRs in its
-// small shape and 65 in the usual one, scheduled for eight waves in the former (6M
+// digest to 66 VGPRs and seven waves).  The BF16-state commit takes 39 VGPRs in its
+// small shape and 64 in the usual one, scheduled for eight waves in the former (6M
 // elements 18.6 us against 19.6) and for six in the latter (453M 1115 us against 1128).
 template <Mode M, Form F>
 constexpr unsigned kMinWavesPerSimd = (M == Mode::StateDigest || M == Mode::DigestBf16State) ? 8u
