@@ -253,7 +253,7 @@ def tile_elements(kernel: str, n: int) -> int:
 
 # Sub-shards of the cache-resident rates: name, bytes per element moved and resident, sizes
 RESIDENT = (("shard_digest", 12, 12, (4 << 20, 8 << 20, 12 << 20, 16 << 20)),
-            ("commit_bf16_state", 14, 8, (17 << 20, 20 << 20, 23 << 20, 26 << 20)))
+            ("commit_bf16_state", 14, 8, (17 << 20, 19 << 20, 21 << 20, 23 << 20)))
 XCDS = 8      # GRBM_GUI_ACTIVE comes back summed over the eight XCDs
 NUM_CUS = 256
 # Nominal VALU issue peak: 256 CUs x 4 SIMDs, each SIMD 16 lanes wide, so one

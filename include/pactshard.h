@@ -272,7 +272,7 @@ int64_t pact_workspace_bytes_bf16(const pact_shard_bf16* s);
  * commit's eight concurrent streams (reads of p, g, m, v; writes of p', m',
  * v' and the bf16 copy) reach about 6.4-6.5 TB/s (80-81% of the 8 TB/s
  * peak) when the arrays sit in separate regions of HBM some tens of GB
- * apart, and about 6.1-6.2 TB/s (77-78%) when they sit within a few GB of
+ * apart, and 5.9-6.3 TB/s (73-79%) when they sit within a few GB of
  * each other -- the case of five back-to-back allocations.  The kernels are
  * the same; the difference is the memory system's.  pact_arena_plan gives
  * the library's placement rule as byte offsets into one pool the caller

@@ -397,7 +397,7 @@ class ShardArena:
     rule (``pact_arena_plan``): each array in its own region of HBM.
 
     On MI355X the commit's eight concurrent streams (reads of p, g, m, v;
-    writes of p', m', v' and the bf16 copy) move about 6.1-6.2 TB/s when all five
+    writes of p', m', v' and the bf16 copy) move 5.9-6.3 TB/s when all five
     arrays sit within a few gigabytes of each other, and about 6.4-6.5 TB/s
     when they are spread over four or five regions some tens of gigabytes
     apart (the same bytes, the same kernel).  The arena takes one device
