@@ -87,6 +87,25 @@ def test_call_after_a_workspace_that_was_not_clear(n):
     assert pk.to_u64(pk.shard_digest(sh)) == want and sh.workspace_clean
 
 
+@pytest.mark.parametrize("n", [3 * T + 7, 70 * T])
+def test_commit_after_a_state_that_was_wrong(n):
+    """A binary32 commit goes by its state: a workspace written to while that says clear costs
+    one digest, from either set, and none of the arrays."""
+    import torch
+
+    pk = _pk()
+    p, g, m, v = _state(n, 9)
+    sh = make_shard(p, g, m, v, 7)
+    b = np.zeros(n, np.uint16)
+    for first in (2, 4, 6):
+        sh.workspace.copy_(torch.randint(1, 256, sh.workspace.shape, dtype=torch.uint8, device=sh.workspace.device))
+        for step in range(first, first + 3):
+            got = pk.to_u64(pk.adamw_commit(sh, step, pk.Hyper(**H)))
+            want = oracle.commit_and_digest(p, g, m, v, b, o_hyper(H), step, 7)
+            assert step == first or got == [want], step
+    assert np.array_equal(sh.param.cpu().numpy().view(np.uint32), p.view(np.uint32))
+
+
 def test_calls_that_change_streams_clear_first():
     """The state vouches for calls on one stream only: after a call on another
     stream the workspace is cleared by the call itself."""
